@@ -282,8 +282,13 @@ wc_status wc_color(wc_ctx *ctx, const wc_csr *g, const uint32_t *prio, int32_t *
  * descendants of v.  A node with children is a recursive call whose work is
  * consolidated per `mode`; a leaf gets 0; the post-work folds each child c
  * into its parent as 1 + desc[c].
- *   WC_FLAT, WC_GRID: level-synchronous (one launch per level, a graph of all
- *     levels replayed by a repeated call), the folds by one bottom-up pass per level.
+ *   WC_GRID, without stats and with block_threads, grid_blocks and
+ *     items_per_lane left to the library: one pass over all child lists, cut
+ *     into tiles of equal work, then the folds from the finished nodes upward
+ *     (two launches whatever the depth; the call only enqueues).
+ *   WC_FLAT, and WC_GRID otherwise: level-synchronous (one launch per level, a
+ *     graph of all levels replayed by a repeated call), the folds by one
+ *     bottom-up pass per level.
  *   WC_WAVE, WC_BLOCK: no grid-wide barrier: a persistent grid whose groups
  *     flush the calls they find as packets of about 64 * items_per_lane (wave)
  *     or block_threads * items_per_lane (block) children into a device-wide
@@ -302,11 +307,13 @@ wc_status wc_tree_height(wc_ctx *ctx, const wc_tree *t, int32_t *height, wc_mode
  * the problem of wc_tree_descendants / wc_tree_height).  trees and desc /
  * height are HOST arrays of `count` entries whose pointers are device arrays
  * (desc[i] has trees[i].n entries and is written entirely; trees[i].parent is
- * not read).  Flat or grid mode for the whole batch: every level kernel takes
- * the items of that depth in all trees, so grid mode consolidates the recursive
- * calls of all trees into one buffer per level (one child per level for the
- * whole batch) and its post-work likewise.  A call repeated with the same
- * trees, outputs, mode and tune replays a HIP graph of all its levels.
+ * not read).  Flat or grid mode for the whole batch: the tiles of all trees in
+ * the two launches of wc_tree_descendants' grid mode; level by level, every
+ * level kernel takes the items of that depth in all trees, so grid mode
+ * consolidates the recursive calls of all trees into one buffer per level (one
+ * child per level for the whole batch) and its post-work likewise, and a call
+ * repeated with the same trees, outputs, mode and tune replays a HIP graph of
+ * all its levels.
  * Results equal the single-tree calls.  WC_EINVAL for wave or block mode, a
  * tree without root, NULL arrays, more than 2^31 nodes in total, or
  * tune->driver != 0. */

@@ -210,6 +210,7 @@ wc_status resolve_tune(wc_ctx *ctx, const char *problem, wc_mode mode, const wc_
         return fail(WC_EINVAL, "buffer_alloc exists for SSSP only");
     out->buf_capacity = t.buf_capacity;
     out->buffer_alloc = t.buffer_alloc;
+    out->own_shape = tune && (tune->block_threads > 0 || tune->grid_blocks > 0 || tune->items_per_lane > 0);
     return WC_OK;
 }
 

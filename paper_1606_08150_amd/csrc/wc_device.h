@@ -29,6 +29,18 @@ __device__ __forceinline__ uint32_t readlane_u(uint32_t v, int lane)
     return (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
 }
 
+// ---- pointers read from memory ------------------------------------------------------------------
+// A pointer that a kernel loads from a descriptor in memory has no known address
+// space, and the compiler accesses it with flat instructions (each also counted
+// as an LDS access).  Device arrays are global: such a pointer is used as a gptr.
+template <typename T>
+using gptr = __attribute__((address_space(1))) T *;
+template <typename T>
+__device__ __forceinline__ gptr<T> global_ptr(T *p)
+{
+    return (gptr<T>)p;
+}
+
 // ---- guarded loads ---------------------------------------------------------------------------
 // arr[i] when ok, else zero, without a select between a global address and a
 // local temporary (which the compiler would otherwise materialise on the stack).

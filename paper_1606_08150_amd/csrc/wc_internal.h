@@ -147,6 +147,7 @@ struct Config {
     bool fail_on_overflow;
     long long buf_capacity;
     int buffer_alloc;
+    bool own_shape;  // the caller set block_threads, grid_blocks or items_per_lane
 };
 
 int resident_blocks(wc_ctx *ctx, const void *kernel, int block);

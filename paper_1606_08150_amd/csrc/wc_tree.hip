@@ -8,9 +8,13 @@
 // Consolidation buffers the recursive calls, i.e. the nodes with children, and
 // one consolidated child processes all buffered nodes' children.
 //
-//   grid  - level-synchronous: the global buffer of level l holds chunks of
-//           the children ranges of every node found in level l-1; a grid-wide
-//           barrier (the kernel boundary) separates levels.  The post-work is consolidated too (Sec. IV.C,
+//   grid  - the recursive calls of the whole grid in one buffer.  Without work
+//           counters and with the library's launch shape: fold tiles, one
+//           grid-wide consolidation of every call's children and one climb of
+//           the post-work (below).  Otherwise level-synchronous: the global
+//           buffer of level l holds chunks of the children ranges of every node
+//           found in level l-1; a grid-wide barrier (the kernel boundary)
+//           separates levels.  The post-work is consolidated too (Sec. IV.C,
 //           grid-level post-work): after the last level, one pass per level from
 //           the deepest up folds every chunk into its node with one atomic.
 //   flat  - the same level structure without consolidation: one thread per
@@ -27,6 +31,7 @@
 // Integer folds are associative and commutative, so every mode and schedule
 // gives identical results.
 #include <algorithm>
+#include <climits>
 #include <cstring>
 #include <string>
 #include <type_traits>
@@ -739,6 +744,247 @@ __global__ void tree_zero_out(TreeArgs a)
     for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < a.n; v += gridDim.x * blockDim.x) a.out[v] = 0;
 }
 
+// ---------------------------------------------------------------- fold tiles (grid mode without work counters)
+//
+// Grid mode's results without the level-by-level schedule: the fold of a
+// node needs its children's values only, so no level has to wait for another.
+//   tree_fold_tiles  - one pass over all nodes and all child entries at once.
+//     The grid-wide work list (every node's child entries, then the node
+//     itself) is cut into tiles of kTile entries of equal size, so a hub's
+//     children spread over many workgroups and a run of leaves costs no more
+//     than its length.  A tile sets its leaves' results, counts each node's
+//     leaf children, records the parent of every child that has children and
+//     leaves each node's post-work word: the children still to come and the
+//     fold of the leaves.  Nodes all of whose children are leaves are final and
+//     go to the tile's list.
+//   tree_fold_climb  - from the finished nodes upward: each folds into its
+//     parent with one atomic, and the child that completes a node carries on
+//     with it.
+// Bound by the gathers of the children's ranges (shuffled ids: a line of 128
+// bytes a child entry, 45 of the 84 us of the tile pass on the 2^22-node tree)
+// and by the round trips of the climb (one a level, two for heights); the level
+// schedule it replaces paid two launches of 6 to 110 us a level.
+// Descendants of 2^22-node random trees of 9 to 23 levels: 485 to 917 -> 104 to
+// 129 us; heights of 64 trees of 2^10 to 2^17 nodes in one call: 575 -> 99 us.
+constexpr int kTile = 2048;        // work-list entries (child entries and nodes) a tile
+constexpr int kTileBlock = 256;
+constexpr int kTileReady = kTile / 2 + 1;  // a final node brings a child entry and, but for the last one, itself
+
+struct FoldTree {
+    const int *child_ptr;
+    const int *child;
+    int *out;
+    int n;
+    int tile0;      // first tile of the tree
+    long long base; // first entry of the tree in `word` and `up`
+};
+
+constexpr int kSole = INT_MIN;
+
+struct FoldArgs {
+    FoldTree one;            // a single tree
+    const FoldTree *trees;   // batch: the trees, and the tree of each tile
+    const int *tile_tree;
+    unsigned long long *word;  // nodes with children: (children still to come << 32) | fold of the finished ones
+    int *up;           // nodes with children: the parent; negative (kSole) where the node is its only inner child
+    int *ready;        // [tiles * kTileReady]: final nodes of each tile
+    int *ready_count;  // [tiles]
+    int2 *carry;       // [tiles]: (node whose entries began in an earlier tile or -1, its leaves here)
+};
+
+// The tree of a tile, its arrays known to be global memory.
+struct FoldView {
+    gptr<const int> child_ptr;
+    gptr<const int> child;
+    gptr<int> out;
+    gptr<unsigned long long> word;
+    gptr<int> up;
+    int n, tile0;
+};
+template <bool BATCH>
+__device__ __forceinline__ FoldView fold_view(const FoldArgs &a, int tile)
+{
+    const FoldTree &t = BATCH ? a.trees[a.tile_tree[tile]] : a.one;
+    return FoldView{global_ptr(t.child_ptr), global_ptr(t.child), global_ptr(t.out),
+                    global_ptr(a.word + t.base), global_ptr(a.up + t.base), t.n, t.tile0};
+}
+
+// Nodes whose entries (children, then themselves) all lie among the first d
+// entries of the work list: a 64-way search by one wave, 3 to 6 dependent loads
+// instead of a binary search's 10 to 31.
+__device__ __forceinline__ int nodes_before(gptr<const int> child_ptr, int n, long long d)
+{
+    int lo = 0, hi = n;  // the answer lies in [lo, hi]
+    while (lo < hi) {
+        const int step = (hi - lo + kWave - 1) / kWave;
+        const long long q = (long long)lo + (long long)step * lane_id() + step - 1;  // is node q among them?
+        const bool in = q < hi && (long long)child_ptr[q + 1] + q + 1 <= d;
+        const int c = __builtin_popcountll(__ballot(in));  // monotone: the first c probes hold
+        const long long nlo = (long long)lo + (long long)c * step;
+        hi = (int)min((long long)hi, nlo + step - 1);
+        lo = (int)min(nlo, (long long)hi);
+    }
+    return lo;
+}
+
+// Folds `count` finished children with the value `contrib` into *w: true for
+// the last ones, with the node's value.  Descendants: one 64-bit add.  Heights:
+// the maximum, then the count; the count is lowered only after the maximum's
+// old value has come back (the empty asm uses it), so whoever takes the count
+// to zero gets the final maximum back with it.  No compare-and-swap, so no
+// retries where many children share a parent.  The words are touched by atomics
+// alone here: reading them first, to skip an atomic, made the climb of the
+// 2^22-node tree three times slower (42 -> 121 us), for every such read leaves
+// a copy of the line in its own XCD's L2 that the next atomic has to reclaim.
+template <int OP>
+__device__ __forceinline__ bool fold_into(unsigned long long *w, int contrib, int count, int &val)
+{
+    unsigned long long add = (unsigned long long)(unsigned int)-count << 32;
+    int got = 0;
+    if (OP == OP_DESC) {
+        add += (unsigned int)contrib;  // never carries: a node's descendants stay below 2^31
+    } else {
+        got = atomic_max_dev(reinterpret_cast<int *>(w), contrib);  // the low half
+        asm volatile("" : : "v"(got) : "memory");
+    }
+    const unsigned long long nw = __hip_atomic_fetch_add(w, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + add;
+    val = (int)(unsigned int)nw;
+    return (nw >> 32) == 0;
+}
+
+// A final node with value val and the given up entry: fold it into its parent
+// and climb on while this completes nodes.  The next up entry is requested
+// beside the fold, so a level costs one or two round trips to memory.
+template <int OP>
+__device__ __forceinline__ void fold_climb(const FoldView &t, int up, int val)
+{
+    for (;;) {
+        const int p = up & ~kSole;
+        const int next = p ? t.up[p] : 0;
+        if (up < 0) val = OP == OP_DESC ? t.out[p] + 1 + val : max(t.out[p], 1 + val);
+        else if (!fold_into<OP>((unsigned long long *)&t.word[p], 1 + val, 1, val)) return;
+        t.out[p] = val;
+        if (p == 0) return;
+        up = next;
+    }
+}
+
+template <int OP, bool BATCH>
+__global__ __launch_bounds__(kTileBlock) void tree_fold_tiles(FoldArgs a)
+{
+    constexpr int E = kTile / kTileBlock;
+    __shared__ int s_ptr[kTile + 2], s_leaf[kTile + 1];
+    __shared__ int s_split[2], s_ready;
+    const int tile = blockIdx.x, tid = threadIdx.x, lane = lane_id();
+    const FoldView t = fold_view<BATCH>(a, tile);
+    const long long total = 2LL * t.n - 1;  // n nodes and n - 1 child entries
+    const long long d0 = (long long)(tile - t.tile0) * kTile, d1 = min(total, d0 + kTile);
+    if (tid / kWave < 2) {
+        const int k = nodes_before(t.child_ptr, t.n, tid < kWave ? d0 : d1);
+        if (lane == 0) s_split[tid / kWave] = k;
+    }
+    if (tid == 0) s_ready = 0;
+    __syncthreads();
+    const int p0 = s_split[0], p1 = s_split[1];
+    const int e0 = (int)(d0 - p0), e1 = (int)(d1 - p1);
+    // the children of the tile, and whether they have children themselves
+    int c[E], f[E], own[E];
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
+        const int e = e0 + k * kTileBlock + tid;
+        c[k] = e < e1 ? t.child[e] : -1;
+    }
+    const int nn = min(p1, t.n - 1) - p0 + 1;  // nodes p0 .. p1, the last one perhaps only begun here
+    for (int i = tid; i <= nn; i += kTileBlock) s_ptr[i] = t.child_ptr[p0 + i];
+    for (int i = tid; i < nn; i += kTileBlock) s_leaf[i] = 0;
+#pragma unroll
+    for (int k = 0; k < E; ++k) f[k] = c[k] >= 0 ? t.child_ptr[c[k] + 1] - t.child_ptr[c[k]] : 0;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
+        const int e = e0 + k * kTileBlock + tid;
+        own[k] = -1;
+        if (c[k] >= 0) {
+            // the node of entry e: the last one whose range begins at or before e
+            int lo = 0, hi = nn - 1;
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (s_ptr[mid] <= e) lo = mid;
+                else hi = mid - 1;
+            }
+            own[k] = lo;
+        }
+        // lanes of one node are neighbours: the first of them counts their leaves
+        const int prev = __shfl_up(own[k], 1, kWave);
+        const bool head = own[k] >= 0 && (lane == 0 || prev != own[k]);
+        const uint64_t heads = __ballot(head), leaves = __ballot(c[k] >= 0 && f[k] == 0);
+        if (head) {
+            const uint64_t after = lane == kWave - 1 ? 0ull : heads & (~0ull << (lane + 1));
+            const uint64_t upto = after ? (1ull << __builtin_ctzll(after)) - 1 : ~0ull;
+            const int cnt = __builtin_popcountll(leaves & upto & (~0ull << lane));
+            if (cnt) atomicAdd(&s_leaf[own[k]], cnt);
+        }
+    }
+    __syncthreads();
+    // inner children: their way up.  A node whose entries all lie in this tile
+    // and that has one inner child needs no counting: that child completes it.
+#pragma unroll
+    for (int k = 0; k < E; ++k)
+        if (c[k] >= 0 && f[k] > 0) {
+            const int i = own[k], b = s_ptr[i], e = s_ptr[i + 1];
+            const bool sole = b >= e0 && e <= e1 && s_leaf[i] == e - b - 1;
+            t.up[c[k]] = (p0 + i) | (sole ? kSole : 0);
+        }
+    // carry: the entries of a node that began in an earlier tile
+    if (tid == 0)
+        a.carry[tile] = s_ptr[0] < e0 && e0 < min(s_ptr[1], e1) ? make_int2(p0, s_leaf[0]) : make_int2(-1, 0);
+    for (int i0 = 0; i0 < nn; i0 += kTileBlock) {
+        const int i = i0 + tid, p = p0 + i;
+        bool final_node = false;
+        if (i < nn) {
+            const int b = s_ptr[i], fan = s_ptr[i + 1] - b;
+            if (fan == 0) {
+                if (p < p1) t.out[p] = 0;
+            } else if (b >= e0 && b < e1) {
+                const int nl = s_leaf[i], fold = OP == OP_DESC ? nl : (nl > 0 ? 1 : 0);
+                final_node = nl == fan;
+                // a sole inner child finds the leaves' fold in the result
+                if (final_node || (nl == fan - 1 && b + fan <= e1)) t.out[p] = fold;
+                else t.word[p] = ((unsigned long long)(unsigned int)(fan - nl) << 32) | (unsigned int)fold;
+            }
+        }
+        const uint64_t m = __ballot(final_node);
+        if (m) {
+            int at = 0;
+            if (lane == 0) at = atomicAdd(&s_ready, __builtin_popcountll(m));
+            at = readlane(at, 0);
+            if (final_node) a.ready[(long long)tile * kTileReady + at + rank_in(m)] = p;
+        }
+    }
+    __syncthreads();
+    if (tid == 0) a.ready_count[tile] = s_ready;
+}
+
+template <int OP, bool BATCH>
+__global__ __launch_bounds__(kTileBlock) void tree_fold_climb(FoldArgs a)
+{
+    const int tile = blockIdx.x;
+    const FoldView t = fold_view<BATCH>(a, tile);
+    const int count = a.ready_count[tile];
+    for (int j = threadIdx.x; j < count; j += kTileBlock) {
+        const int p = a.ready[(long long)tile * kTileReady + j];
+        if (p) fold_climb<OP>(t, t.up[p], t.out[p]);
+    }
+    if (threadIdx.x == kTileBlock - 1) {
+        const int2 c = a.carry[tile];
+        int val = 0;
+        if (c.x >= 0 && c.y > 0 && fold_into<OP>((unsigned long long *)&t.word[c.x], OP == OP_DESC ? c.y : 1, c.y, val)) {
+            t.out[c.x] = val;
+            if (c.x) fold_climb<OP>(t, t.up[c.x], val);
+        }
+    }
+}
+
 // ---------------------------------------------------------------- host side
 
 template <int OP, int BLOCK>
@@ -764,6 +1010,82 @@ TreeKernels<OP, BLOCK> kernels_for(wc_mode mode)
     return k;
 }
 
+// Fold tiles over one tree or a batch: workspace of the two kernels.
+struct FoldPlan {
+    long long nodes = 0, tiles = 0;
+    size_t desc_bytes = 0;  // batch: descriptors and the tree of each tile
+    size_t bytes() const
+    {
+        return padded(nodes * 8) + padded(nodes * 4) + padded(tiles * kTileReady * 4) + padded(tiles * 4) +
+               padded(tiles * 8) + padded(desc_bytes);
+    }
+};
+
+FoldPlan plan_fold(const TreeArgs &a, const std::vector<TreeInst> *batch)
+{
+    FoldPlan f;
+    auto add = [&](long long n) {
+        f.nodes += n;
+        f.tiles += (2 * n - 1 + kTile - 1) / kTile;
+    };
+    if (!batch) {
+        add(a.n);
+    } else {
+        for (const TreeInst &t : *batch) add(t.n);
+        f.desc_bytes = padded(sizeof(FoldTree) * batch->size()) + sizeof(int) * (size_t)f.tiles;
+    }
+    return f;
+}
+
+template <int OP>
+wc_status run_fold(wc_ctx *ctx, const TreeArgs &t, const FoldPlan &f, const std::vector<TreeInst> *batch,
+                   hipStream_t stream)
+{
+    FoldArgs a;
+    std::memset(&a, 0, sizeof(a));
+    a.word = pool_take<unsigned long long>(ctx, f.nodes);
+    a.up = pool_take<int>(ctx, f.nodes);
+    a.ready = pool_take<int>(ctx, f.tiles * kTileReady);
+    a.ready_count = pool_take<int>(ctx, f.tiles);
+    a.carry = pool_take<int2>(ctx, f.tiles);
+    chain_break(ctx);
+    if (!batch) {
+        a.one = FoldTree{t.child_ptr, t.child, t.out, t.n, 0, 0};
+    } else {
+        char *dev = pool_take<char>(ctx, f.desc_bytes);
+        std::vector<char> host(f.desc_bytes);
+        FoldTree *tr = reinterpret_cast<FoldTree *>(host.data());
+        const size_t table = padded(sizeof(FoldTree) * batch->size());
+        int *tile_tree = reinterpret_cast<int *>(host.data() + table);
+        long long base = 0;
+        int tile = 0;
+        for (size_t i = 0; i < batch->size(); ++i) {
+            const TreeInst &b = (*batch)[i];
+            tr[i] = FoldTree{b.child_ptr, b.child, b.out, (int)b.n, tile, base};
+            const int k = (int)((2 * b.n - 1 + kTile - 1) / kTile);
+            std::fill(tile_tree + tile, tile_tree + tile + k, (int)i);
+            tile += k;
+            base += b.n;
+        }
+        wc_status st = stage_to_device(ctx, dev, host.data(), f.desc_bytes, stream);
+        if (st != WC_OK) return st;
+        a.trees = reinterpret_cast<const FoldTree *>(dev);
+        a.tile_tree = reinterpret_cast<const int *>(dev + table);
+    }
+    void *args[] = {&a};
+    wc_status st = launch(ctx, "tree_fold_tiles", batch ? reinterpret_cast<const void *>(&tree_fold_tiles<OP, true>)
+                                      : reinterpret_cast<const void *>(&tree_fold_tiles<OP, false>),
+                          dim3((unsigned)f.tiles), dim3(kTileBlock), args, stream);
+    if (st == WC_OK)
+        st = launch(ctx, "tree_fold_climb",
+                    batch ? reinterpret_cast<const void *>(&tree_fold_climb<OP, true>)
+                          : reinterpret_cast<const void *>(&tree_fold_climb<OP, false>),
+                    dim3((unsigned)f.tiles), dim3(kTileBlock), args, stream);
+    if (st != WC_OK) return st;
+    WC_HIP(hipGetLastError());
+    return WC_OK;
+}
+
 // The level-synchronous modes (flat, grid) over one tree or a batch of trees
 // (all trees' items of one depth in the same level buffer).  n: total nodes,
 // max_n: nodes of the largest tree (bounds the depth).
@@ -781,8 +1103,16 @@ wc_status run_levels(wc_ctx *ctx, TreeArgs a, wc_mode mode, const Config &cfg, i
     long long cap = mode == WC_GRID ? n + n / chunk + 2LL * count : n + count;
     const size_t inst_bytes = batch ? sizeof(TreeInst) * batch->size() : 0;
     size_t need = 2 * padded(lvl_len * 4) + padded(cap * 16) + padded(inst_bytes);
+    // The fold tiles serve grid mode where the launch shape is the library's
+    // choice and no work is counted: the counters of wc_stats and an explicit
+    // workgroup size, grid or chunk size describe the level-by-level execution.
+    // The plan covers both, so one made without counters serves a call with them.
+    const bool tiles = mode == WC_GRID && !cfg.own_shape;
+    const FoldPlan fold = tiles ? plan_fold(a, batch) : FoldPlan{};
+    if (tiles) need = std::max(need, fold.bytes());
     wc_status st = pool_reserve(ctx, need, stream);
     if (st != WC_OK) return st;
+    if (tiles && !stats) return run_fold<OP>(ctx, a, fold, batch, stream);
     a.lvl_start = pool_take<int>(ctx, lvl_len);
     a.lvl_count = pool_take<int>(ctx, lvl_len);
     a.items = pool_take<int4>(ctx, cap);
