@@ -49,6 +49,7 @@ constexpr int kChunkBin = 7;  // rows split into whole-wave chunks
 constexpr int kUnroll = 4;    // nonzeros in flight per lane
 constexpr int kMultiCol = 8;  // column of the per-block counts holding split rows
 constexpr int kCols = 9;
+constexpr int kPad = 32;  // the bins' counters live on separate 128-byte lines
 
 struct SpmvArgs {
     const int *row_ptr;
@@ -67,15 +68,16 @@ struct SpmvArgs {
     int chunk;         // 64 * ipl
     int spill;         // wave and block modes: buffered rows longer than this go to the global chunks
     int count_drain;   // grid mode: the drain counts as the consolidated dispatch
+    int windows;       // grid mode: windows of a binning step, 1 .. kWindows
     // grid mode
-    int *blk_count;    // [grid * kCols]: per parent block, rows per bin 0..6, chunks, split rows
-    int *blk_off;      // [grid * kCols]: exclusive offsets of each block within its column
-    int *bin_total;    // [kCols]: column totals
-    int4 *rows_buf;    // binned rows: (row, begin, end, 0), bins laid out by prefix of totals
-    long long rows_cap;
-    int4 *chunks;      // (row, begin, end, 0)
+    int *bin_total;    // [kCols * kPad]: rows per bin 0..6, chunks, split rows; zeroed before the parent
+    int *rows_buf;     // binned rows, see bin_entry
+    long long bin_off[kBins + 1];
+    long long rows_cap;  // driver 2: entries of `basic`
+    int4 *basic;       // driver 2: (row, begin, end, 0)
+    int4 *chunks;      // (row, begin, end, entry in multi)
     long long chunk_cap;
-    int4 *multi;       // (row, first chunk, chunk count, 0)
+    int4 *multi;       // (row, first chunk, chunk count, chunks still to be summed)
     long long multi_cap;
     float *partials;   // one per chunk slot
     DevStats *stats;
@@ -136,13 +138,28 @@ __device__ __forceinline__ float group_sum(float v, int g)
     return v;
 }
 
+// log2 of the lane group of a row of len entries: the smallest power of two g
+// with g * ipl >= len.  Called with 64 * ipl >= len; counted, not divided.
 __device__ __forceinline__ int bin_of(int len, int ipl)
 {
-    // g = smallest power of two with g * ipl >= len, as a bin index (log2 g)
-    int need = (len + ipl - 1) / ipl;
     int b = 0;
-    while ((1 << b) < need) ++b;
+#pragma unroll
+    for (int k = 0; k < kBins - 1; ++k) b += len > ipl << k ? 1 : 0;
     return b;
+}
+
+// A light row (up to kLight entries, more with a larger threshold), summed by
+// its lane.
+constexpr int kLight = 2 * kUnroll;
+__device__ __forceinline__ float light_row(const SpmvArgs &a, int beg, int end)
+{
+    return dot_strided_u<kLight>(a, beg, 1, end);
+}
+
+// Entry i of bin b in rows_buf: even bins grow upward, odd ones downward.
+__device__ __forceinline__ long long bin_entry(const SpmvArgs &a, int b, int i)
+{
+    return b & 1 ? a.bin_off[b] - i : a.bin_off[b] + i;
 }
 
 template <int BLOCK>
@@ -170,34 +187,33 @@ __device__ __forceinline__ void count_stats(StatAcc &acc, int len, bool heavy, b
 // fallback) and its reserved entries are marked empty.  Every lane calls this.
 __device__ __forceinline__ void spill_rows(const SpmvArgs &a, int r, int beg, int end, int nch)
 {
-    const int slot = wave_reserve_n(nch, &a.bin_total[kChunkBin]);
-    const int mslot = wave_reserve(nch > 0, &a.bin_total[kMultiCol]);
+    const int slot = wave_reserve_n(nch, &a.bin_total[kChunkBin * kPad]);
+    const int mslot = wave_reserve(nch > 0, &a.bin_total[kMultiCol * kPad]);
     const bool fits = nch > 0 && (long long)slot + nch <= a.chunk_cap && mslot < a.multi_cap;
     uint64_t m = __ballot(fits);
     while (m) {
         const int b = __builtin_ctzll(m);
         m &= m - 1;
         const int s0 = readlane(slot, b), n0 = readlane(nch, b), rb = readlane(beg, b), re = readlane(end, b);
-        const int rr = readlane(r, b);
+        const int rr = readlane(r, b), rm = readlane(mslot, b);
         for (int c = lane_id(); c < n0; c += kWave) {
             const int cb = rb + c * a.chunk;
-            a.chunks[s0 + c] = make_int4(rr, cb, min(re, cb + a.chunk), 0);
+            a.chunks[s0 + c] = make_int4(rr, cb, min(re, cb + a.chunk), rm);
         }
     }
-    if (fits) a.multi[mslot] = make_int4(r, slot, nch, 0);
+    if (fits) a.multi[mslot] = make_int4(r, slot, nch, nch);
     if (nch > 0 && !fits) {
         for (int c = 0; c < nch; ++c)
             if ((long long)slot + c < a.chunk_cap) a.chunks[slot + c] = make_int4(-1, 0, 0, 0);
-        if (mslot < a.multi_cap) a.multi[mslot] = make_int4(-1, 0, 0, 0);
         a.stats->overflowed = 1;
         a.y[r] = dot_strided(a, beg, 1, end);
     }
 }
 
-// Zeroes the bin totals before a wave- or block-mode parent reserves chunks.
+// Zeroes the bin totals before a parent reserves entries of its buffers.
 __global__ void spmv_reset(SpmvArgs a)
 {
-    if (threadIdx.x < kCols) a.bin_total[threadIdx.x] = 0;
+    if (threadIdx.x < kCols) a.bin_total[threadIdx.x * kPad] = 0;
 }
 
 // Parent kernel of the flat, wave and block modes.
@@ -300,174 +316,109 @@ __global__ __launch_bounds__(BLOCK) void spmv_parent(SpmvArgs a)
 
 // ---- grid mode --------------------------------------------------------------------------------
 
-// Counting pass: each parent block counts, over exactly the rows it will take
-// in the parent pass, its rows per bin, its chunks of split rows and its split
-// rows.  No atomics: one row of counts per block.
-template <int BLOCK>
-__global__ __launch_bounds__(BLOCK) void spmv_classify(SpmvArgs a)
-{
-    __shared__ int cnt[kCols];
-    if (threadIdx.x < kCols) cnt[threadIdx.x] = 0;
-    __syncthreads();
-    int mine[kCols];
-#pragma unroll
-    for (int c = 0; c < kCols; ++c) mine[c] = 0;
-    // four windows' row lengths are requested together
-    constexpr int W = 4;
-    const int stride = gridDim.x * BLOCK;
-    for (long long base0 = (long long)blockIdx.x * BLOCK; base0 < a.n; base0 += (long long)W * stride) {
-        int lens[W];
-#pragma unroll
-        for (int w = 0; w < W; ++w) {
-            const long long r = base0 + (long long)w * stride + threadIdx.x;
-            lens[w] = r < a.n ? a.row_ptr[r + 1] - a.row_ptr[r] : 0;
-        }
-#pragma unroll
-        for (int w = 0; w < W; ++w) {
-            const int len = lens[w];
-            if (len > a.threshold) {
-                if (len > a.chunk) {
-                    mine[kChunkBin] += (len + a.chunk - 1) / a.chunk;
-                    mine[kMultiCol] += 1;
-                } else {
-                    const int b = bin_of(len, a.ipl);
-#pragma unroll
-                    for (int c = 0; c < kBins; ++c) mine[c] += c == b;
-                }
-            }
-        }
-    }
-#pragma unroll
-    for (int c = 0; c < kCols; ++c) {
-        int v = wave_sum_i(mine[c]);
-        if (lane_id() == 0 && v) atomicAdd(&cnt[c], v);
-    }
-    __syncthreads();
-    if (threadIdx.x < kCols) a.blk_count[blockIdx.x * kCols + threadIdx.x] = cnt[threadIdx.x];
-}
-
-// Exclusive scan of the per-block counts down each column: one workgroup, one
-// wave per column; a wave requests 16 x 64 counts at once, then scans them
-// with wave scans and a running carry (no barriers).
-__global__ __launch_bounds__(kCols * kWave) void spmv_scan(SpmvArgs a, int nblocks)
-{
-    constexpr int K = 16;
-    const int c = threadIdx.x / kWave, lane = lane_id();
-    int carry = 0;
-    for (int b0 = 0; b0 < nblocks; b0 += K * kWave) {
-        int v[K];
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const int b = b0 + k * kWave + lane;
-            v[k] = b < nblocks ? a.blk_count[b * kCols + c] : 0;
-        }
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const int b = b0 + k * kWave + lane;
-            const int incl = wave_incl_scan(v[k]);
-            if (b < nblocks) a.blk_off[b * kCols + c] = carry + incl - v[k];
-            carry += __shfl(incl, kWave - 1, kWave);
-        }
-    }
-    if (lane == 0) a.bin_total[c] = carry;
-}
-
-// Parent pass of grid mode: light rows inline, heavy rows written into their
-// bin at the offsets the scan gave this block.  STATS: the instantiation that
-// counts work for wc_stats (without it no counters are kept live).
+// Parent pass of grid mode: heavy rows into the buffers of their bins, light
+// rows summed inline.  A block counts its rows of up to kWindows windows per bin
+// with LDS atomics, which also give each row its place, reserves the entries
+// with one atomic per bin, and sums its light rows while that is on its way.  A
+// row's sum depends on its own range only, so the order in which rows get their
+// places does not show in y.  Bound by latency and by the gathers of the light
+// rows' x.  A count pass, a scan over all blocks and a parent took three
+// launches: scale-22 graph 105 -> 80 us (about 40 of them for the light rows),
+// 200,003 rows 30 -> 13 us.  Ranking the rows by ballots took 82 and 16 us; the
+// light rows in workgroups of their own, or flattened over the wave's lanes, or
+// in the drain gained nothing.
+// STATS: the instantiation that counts work for wc_stats.
+constexpr int kWindows = 4;
 template <int BLOCK, bool STATS>
-__global__ __launch_bounds__(BLOCK) void spmv_parent_grid(SpmvArgs a)
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8))) void spmv_parent_grid(SpmvArgs a)
 {
-    __shared__ int cur[kCols], binoff[kBins], cnt[kCols];
+    constexpr int kPosBits = 27;  // a block's chunks of one step: fewer than 2^31 / 64 entries
+    __shared__ int s_cnt[kCols], s_base[kCols];
+    __shared__ int s_where[kWindows][BLOCK];  // (bin << kPosBits) | place in the block's share of it; -1: light
+    const int lane = lane_id(), tid = threadIdx.x;
+    const int W = a.windows;
     StatAcc acc;
-    if (threadIdx.x < kCols) cur[threadIdx.x] = a.blk_off[blockIdx.x * kCols + threadIdx.x];
-    if (threadIdx.x == 0) {
-        int o = 0;
-        for (int b = 0; b < kBins; ++b) {
-            binoff[b] = o;
-            o += a.bin_total[b];
+    // a block's windows lie a whole grid apart: neighbouring rows are often alike
+    // (a power-law graph's hubs have small ids), and the hubs' chunks take longest
+    const long long stride = (long long)gridDim.x * BLOCK;
+    for (long long base = (long long)blockIdx.x * BLOCK; base < a.n; base += W * stride) {
+        int len[kWindows];
+#pragma unroll
+        for (int w = 0; w < kWindows; ++w) {
+            const long long r = base + w * stride + tid;
+            len[w] = w < W && r < a.n ? a.row_ptr[r + 1] - a.row_ptr[r] : 0;
         }
-    }
-    for (int base = blockIdx.x * BLOCK; base < a.n; base += gridDim.x * BLOCK) {
-        if (threadIdx.x < kCols) cnt[threadIdx.x] = 0;
+        if (tid < kCols) s_cnt[tid] = 0;
         __syncthreads();
-        const int r = base + threadIdx.x;
-        const bool valid = r < a.n;
-        int beg = 0, end = 0;
-        if (valid) {
-            beg = a.row_ptr[r];
-            end = a.row_ptr[r + 1];
-        }
-        const int len = end - beg;
-        const bool heavy = len > a.threshold;
-        if (STATS) count_stats(acc, len, heavy, false);
-        if (valid && !heavy) a.y[r] = dot_strided_u<2 * kUnroll>(a, beg, 1, end);
-        int bin = -1, local = 0, nch = 0, mlocal = 0;
-        if (heavy) {
-            if (len > a.chunk) {
-                bin = kChunkBin;
-                nch = (len + a.chunk - 1) / a.chunk;
-                local = atomicAdd(&cnt[kChunkBin], nch);
-                mlocal = atomicAdd(&cnt[kMultiCol], 1);
-            } else {
-                bin = bin_of(len, a.ipl);
-                local = atomicAdd(&cnt[bin], 1);
+#pragma unroll
+        for (int w = 0; w < kWindows; ++w) {
+            if (w >= W) break;
+            const bool heavy = len[w] > a.threshold;
+            if (STATS) count_stats(acc, len[w], heavy, false);
+            int where = -1;
+            if (heavy) {
+                const bool split = len[w] > a.chunk;
+                const int bin = split ? kChunkBin : bin_of(len[w], a.ipl);
+                where = bin << kPosBits | atomicAdd(&s_cnt[bin], split ? (len[w] + a.chunk - 1) / a.chunk : 1);
+                if (split) atomicAdd(&s_cnt[kMultiCol], 1);
             }
+            s_where[w][tid] = where;
         }
         __syncthreads();
-        if (bin >= 0 && bin < kBins) {
-            const long long pos = (long long)binoff[bin] + cur[bin] + local;
-            if (pos < a.rows_cap) a.rows_buf[pos] = make_int4(r, beg, end, 0);
+        int at = 0;
+        if (tid < kCols && s_cnt[tid]) at = atomic_add_dev(&a.bin_total[tid * kPad], s_cnt[tid]);
+#pragma unroll 1
+        for (int w = 0; w < W; ++w) {
+            const long long r = base + w * stride + tid;
+            if (r < a.n && s_where[w][tid] < 0) a.y[r] = light_row(a, a.row_ptr[r], a.row_ptr[r + 1]);
         }
-        // split rows: the wave writes each such row's chunks together (a long
-        // row's chunks are not left to its own lane)
-        const int slot = cur[kChunkBin] + local;
-        const bool split_fits = bin == kChunkBin && (long long)slot + nch <= a.chunk_cap;
-        uint64_t cm = __ballot(split_fits);
-        while (cm) {
-            const int b = __builtin_ctzll(cm);
-            cm &= cm - 1;
-            const int s0 = readlane(slot, b), n0 = readlane(nch, b);
-            const int rb = readlane(beg, b), re = readlane(end, b), rr = readlane(r, b);
-            for (int c = lane_id(); c < n0; c += kWave) {
-                const int cb = rb + c * a.chunk;
-                a.chunks[s0 + c] = make_int4(rr, cb, min(re, cb + a.chunk), 0);
+        if (tid < kCols) s_base[tid] = at;
+        __syncthreads();
+#pragma unroll 1
+        for (int w = 0; w < W; ++w) {
+            const int where = s_where[w][tid], bin = where < 0 ? -1 : where >> kPosBits;
+            const int pos = where & ((1 << kPosBits) - 1);
+            const int r = (int)(base + w * stride + tid);
+            if (bin >= 0 && bin < kBins) a.rows_buf[bin_entry(a, bin, s_base[bin] + pos)] = r;
+            // split rows: the wave writes their chunks side by side, chunk j of the
+            // wave belonging to the last row whose chunks begin at or before j
+            const bool split = bin == kChunkBin;
+            const uint64_t sm = __ballot(split);
+            if (!sm) continue;
+            const int rb = split ? a.row_ptr[r] : 0, re = split ? a.row_ptr[r + 1] : 0;
+            const int nch = (re - rb + a.chunk - 1) / a.chunk;
+            const int slot = s_base[kChunkBin] + pos;
+            int mslot = 0;  // entries of the block's split rows, in any order
+            if (split) mslot = s_base[kMultiCol] + atomicAdd(&s_cnt[kMultiCol], -1) - 1;
+            const bool fits = split && (long long)slot + nch <= a.chunk_cap;
+            const int take = fits ? nch : 0, incl = wave_incl_scan(take), pre = incl - take;
+            const int chunks = readlane(incl, kWave - 1);
+            for (int j0 = 0; j0 < chunks; j0 += kWave) {
+                const int j = j0 + lane;
+                int own = 0;
+#pragma unroll
+                for (int d = kWave / 2; d >= 1; d >>= 1) own += __shfl(pre, own + d, kWave) <= j ? d : 0;
+                const int c = j - __shfl(pre, own, kWave);
+                const int cb = __shfl(rb, own, kWave) + c * a.chunk, e0 = __shfl(re, own, kWave);
+                const int s0 = __shfl(slot, own, kWave), rr = __shfl(r, own, kWave), rm = __shfl(mslot, own, kWave);
+                if (j < chunks) a.chunks[s0 + c] = make_int4(rr, cb, min(e0, cb + a.chunk), rm);
             }
-        }
-        if (bin == kChunkBin) {
-            const long long mpos = (long long)cur[kMultiCol] + mlocal;
-            if (split_fits) {
-                if (mpos < a.multi_cap) a.multi[mpos] = make_int4(r, slot, nch, 0);
-            } else {
-                // buffer full: mark the reserved slots that exist as empty and
-                // sum the row inline (fallback); its split-row entry combines nothing
+            if (fits) {
+                a.multi[mslot] = make_int4(r, slot, nch, nch);
+            } else if (split) {
+                // buffer full: mark the reserved slots that exist as empty and sum
+                // the row inline (fallback); no chunk refers to its split-row entry
                 for (int c = 0; c < nch; ++c)
                     if ((long long)slot + c < a.chunk_cap) a.chunks[slot + c] = make_int4(-1, 0, 0, 0);
                 a.stats->overflowed = 1;
-                a.y[r] = dot_strided(a, beg, 1, end);
-                if (mpos < a.multi_cap) a.multi[mpos] = make_int4(-1, 0, 0, 0);
+                a.y[r] = dot_strided(a, rb, 1, re);
             }
         }
-        __syncthreads();
-        if (threadIdx.x < kCols) cur[threadIdx.x] += cnt[threadIdx.x];
+        __syncthreads();  // the counts are cleared by the next step
     }
     if (STATS) stat_flush(a.stats, acc);
 }
 
-// Grid mode with the buffers of an earlier product on the same matrix still in
-// place (PageRank's later sweeps): only the rows up to the threshold, summed
-// inline as spmv_parent_grid sums them; the binned rows and chunks are reused.
-template <int BLOCK>
-__global__ __launch_bounds__(BLOCK) void spmv_light_rows(SpmvArgs a)
-{
-    for (int r = blockIdx.x * BLOCK + threadIdx.x; r < a.n; r += gridDim.x * BLOCK) {
-        const int beg = a.row_ptr[r], end = a.row_ptr[r + 1];
-        if (end - beg <= a.threshold) a.y[r] = dot_strided_u<2 * kUnroll>(a, beg, 1, end);
-    }
-}
-
-// Consolidated child of grid mode.  Wave tasks: for bin b (g = 2^b lanes per
-// row) a task is 64 / g consecutive rows of the bin; then one task per chunk.
 // Hot x values staged in LDS by the drain of the hot-column layout: 32 per
 // thread, at most 16384 (64 KiB), so that four waves per SIMD stay resident.
 template <int BLOCK>
@@ -478,85 +429,221 @@ struct DrainLds {
     float x[HOT ? lds_hot_for<BLOCK>() : 1];
 };
 
-template <int BLOCK, bool HOT>
+// Consolidated child of grid mode.  Wave tasks: first one task per chunk of the
+// split rows; then, for bin b (g = 2^b lanes per row), 64 / g consecutive rows
+// of the bin a task.  LIGHT: the buffers of an earlier product on the same
+// matrix are still in place (PageRank's later sweeps), and the rows up to the
+// threshold, which the parent sums otherwise, come last, 64 a task.
+// The entry of a wave's next task is requested before the current one's
+// entries.
+// Post-work of split rows, by the wave whose chunk is the row's last one to be
+// done: the row's partials summed in chunk order, whoever does it.  A wave's
+// partials have reached memory (the wait) before it lowers the rows' counts,
+// and the counts go down by atomics alone, so the wave that takes one to zero
+// finds every partial.  The counts are lowered between the wave's chunks and
+// its other tasks, which hide the round trips (counting after every chunk cost
+// 17 us of the scale-22 product, this 7, a kernel of its own a launch), and are
+// left as they were found, for the next product on the same buffers.
+// Bound by the gathers of x, a line request a lane: 62M of them in 433 us on the
+// scale-22 graph, a bare gather of its 67M columns 385 us.
+__device__ __forceinline__ void combine_rows(const SpmvArgs &a, int mi, int left)
+{
+    asm volatile("" : : "v"(left) : "memory");
+    for (uint64_t m = __ballot(left == 1); m; m &= m - 1) {
+        int4 *q = &a.multi[readlane(mi, __builtin_ctzll(m))];
+        const int row = q->x, first = q->y, cnt = q->z;
+        Cascade cs;
+        for (int k = lane_id(); k < cnt; k += kWave)
+            cs.add(__hip_atomic_load(&a.partials[first + k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        const float s = wave_sum(cs.total());
+        if (lane_id() == 0) {
+            a.y[row] = s;
+            q->w = cnt;
+        }
+    }
+}
+
+template <int BLOCK, bool HOT, bool LIGHT>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(HOT ? 4 : 8))) void spmv_drain(SpmvArgs a)
 {
-    __shared__ int s_cnt[8], s_off[8], s_task[9];
+    constexpr int kKinds = kBins + 1;  // chunks, the bins; then the light rows
+    __shared__ int s_cnt[kKinds], s_task[kKinds + 2];
     __shared__ DrainLds<BLOCK, HOT> s_x;
     const int nlds = HOT ? min(a.hot, lds_hot_for<BLOCK>()) : 0;
     if (HOT)
         for (int i = threadIdx.x; i < nlds; i += BLOCK) s_x.x[i] = a.x_hot[i];
     if (threadIdx.x == 0) {
-        int o = 0, t = 0;
-        for (int b = 0; b < 8; ++b) {
-            int c = a.bin_total[b];
-            if (b == kChunkBin) c = (long long)c < a.chunk_cap ? c : (int)a.chunk_cap;
-            s_cnt[b] = c;
-            s_off[b] = o;
-            if (b < kBins) o += c;
-            s_task[b] = t;
-            t += b < kBins ? (c + (kWave >> b) - 1) / (kWave >> b) : c;
+        int t = 0;
+        for (int k = 0; k < kKinds; ++k) {
+            int c = a.bin_total[(k ? k - 1 : kChunkBin) * kPad];
+            if (k == 0) c = (long long)c < a.chunk_cap ? c : (int)a.chunk_cap;
+            s_cnt[k] = c;
+            s_task[k] = t;
+            t += k ? (c + (kWave >> (k - 1)) - 1) / (kWave >> (k - 1)) : c;
         }
-        s_task[8] = t;
+        s_task[kKinds] = t;
         if (a.want_stats && a.count_drain && blockIdx.x == 0 && t > 0)
             atomic_add_dev(&a.stats->rep[0].dispatches, 1ull);
+        if (LIGHT) t += (int)(((long long)a.n + kWave - 1) / kWave);
+        s_task[kKinds + 1] = t;
     }
     __syncthreads();
-    const int total = s_task[8];
-    const int gw = (blockIdx.x * BLOCK + threadIdx.x) / kWave;
+    // a wave's task, its kind and its position are uniform and kept so
+    const int total = __builtin_amdgcn_readfirstlane(s_task[kKinds + 1]);
+    const int chunks = __builtin_amdgcn_readfirstlane(s_cnt[0]);
+    const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    const int gw = blockIdx.x * (BLOCK / kWave) + wid;
     const int nw = gridDim.x * (BLOCK / kWave);
     const int lane = lane_id();
-    for (int t = gw; t < total; t += nw) {
-        int b = 0;
-        while (b < 7 && s_task[b + 1] <= t) ++b;
-        // bin task: groups of g lanes per row; chunk task: the whole wave on
-        // one chunk (g = 64).  One code path, so one copy of the dot product.
-        const bool chunk = b >= kBins;
-        const int g = chunk ? kWave : 1 << b;
-        const int sub = lane & (g - 1);
-        int first = 0, end = 0, dst = -1;
-        if (chunk) {
-            const int c = t - s_task[kChunkBin];
-            const int4 d = a.chunks[c];
-            if (__builtin_amdgcn_readfirstlane(d.x) >= 0) {
-                first = __builtin_amdgcn_readfirstlane(d.y) + lane;
-                end = __builtin_amdgcn_readfirstlane(d.z);
-                dst = c;
-            }
-        } else {
-            const int i = (t - s_task[b]) * (kWave >> b) + (lane >> b);
-            if (i < s_cnt[b]) {
-                const int4 d = a.rows_buf[s_off[b] + i];
-                first = d.y + sub;
-                end = d.z;
-                dst = d.x;
-            }
+    int t = gw, mi = -1, left = 0;  // lane k: split-row entry of the wave's k-th chunk, the row's count before it was lowered
+    while (t < chunks) {
+        combine_rows(a, mi, left);  // a wave has more than 64 chunks
+        mi = -1;
+        for (int k = 0; k < kWave && t < chunks; ++k, t += nw) {
+            const int4 d = a.chunks[t];
+            const int row = __builtin_amdgcn_readfirstlane(d.x), from = __builtin_amdgcn_readfirstlane(d.y);
+            const int to = __builtin_amdgcn_readfirstlane(d.z), entry = __builtin_amdgcn_readfirstlane(d.w);
+            const float s = wave_sum(dot_strided_u<2 * kUnroll>(a, from + lane, kWave, to, s_x.x, nlds));
+            if (lane == 0) __hip_atomic_store(&a.partials[t], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (lane == k) mi = row < 0 ? -1 : entry;
         }
-        float s = dot_strided_u<2 * kUnroll>(a, first, g, end, s_x.x, nlds);
-        s = group_sum(s, g);
-        if (dst >= 0 && sub == 0) {
-            if (chunk) a.partials[dst] = s;
-            else a.y[dst] = s;
+        asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+        left = mi >= 0 ? atomic_add_dev(&a.multi[mi].w, -1) : 0;
+    }
+    const int bins_end = __builtin_amdgcn_readfirstlane(s_task[kKinds]);
+    int kind = 1;
+    // the lane's row in task t of a bin (-1: none); the kind only moves forward
+    auto fetch = [&](int at) -> int {
+        int r = -1;
+        if (at < bins_end) {
+            while (__builtin_amdgcn_readfirstlane(s_task[kind + 1]) <= at) ++kind;
+            const int k = at - __builtin_amdgcn_readfirstlane(s_task[kind]);
+            const int i = k * (kWave >> (kind - 1)) + (lane >> (kind - 1));
+            if (i < s_cnt[kind]) r = a.rows_buf[bin_entry(a, kind - 1, i)];
+        }
+        return r;
+    };
+    int row = fetch(t);
+    for (; t < bins_end; t += nw) {
+        const int g = 1 << (kind - 1), sub = lane & (g - 1), dst = row;
+        const int first = dst >= 0 ? a.row_ptr[dst] : 0, end = dst >= 0 ? a.row_ptr[dst + 1] : 0;
+        row = fetch(t + nw);
+        const float s = group_sum(dot_strided_u<2 * kUnroll>(a, first + sub, g, end, s_x.x, nlds), g);
+        if (dst >= 0 && sub == 0) a.y[dst] = s;
+    }
+    if constexpr (LIGHT) {
+        for (; t < total; t += nw) {
+            const long long r = (long long)(t - bins_end) * kWave + lane;
+            const int beg = r < a.n ? a.row_ptr[r] : 0, end = r < a.n ? a.row_ptr[r + 1] : 0;
+            if (r < a.n && end - beg <= a.threshold) a.y[r] = light_row(a, beg, end);
         }
     }
+    combine_rows(a, mi, left);
 }
 
-// Post-work of split rows: the chunk partials of each row, summed in chunk order.
-template <int BLOCK>
-__global__ __launch_bounds__(BLOCK) void spmv_combine(SpmvArgs a)
+// ---- small products -----------------------------------------------------------------------------
+
+// A whole product of grid mode in one launch, for matrices whose buffers a
+// workgroup's LDS holds: a workgroup takes 8 rows, its first wave bins them,
+// and its waves take the same tasks as the grid-wide child (lane groups per
+// row, chunks of the split rows with their partials in LDS, the light rows one
+// lane each), so every sum has the order of the general path.  A workgroup's
+// rows lie a grid apart (hubs often have neighbouring ids).  Rule: up to
+// kSmallNnz entries; 8 rows fill the lane groups of seven bins worse than all
+// rows of the matrix do.  R-MAT, 16 entries a row, this kernel / the general
+// path: 4,096 rows 9.6 / 16.6 us (23.5 before), 16,384 rows (2^18 entries) 13.1
+// / 16.6, 32,768 rows 20.0 / 17.3, 131,072 rows 77 / 26.
+// Bound by launch and memory latency.
+constexpr int kSmallBlock = 512;
+constexpr int kSmallRows = 8;
+constexpr int kSmallNnz = 1 << 18;
+constexpr int kSmallChunk = 512;  // smallest chunk it is used with
+__global__ __launch_bounds__(kSmallBlock) void spmv_small(SpmvArgs a)
 {
-    const int total = (int)min((long long)a.bin_total[kMultiCol], a.multi_cap);
-    const int gw = (blockIdx.x * BLOCK + threadIdx.x) / kWave;
-    const int nw = gridDim.x * (BLOCK / kWave);
-    for (int i = gw; i < total; i += nw) {
-        int4 d = a.multi[i];
-        const int row = __builtin_amdgcn_readfirstlane(d.x);
-        if (row < 0) continue;
-        int first = __builtin_amdgcn_readfirstlane(d.y), cnt = __builtin_amdgcn_readfirstlane(d.z);
+    constexpr int NW = kSmallBlock / kWave;
+    __shared__ int s_row[kWave], s_beg[kWave], s_end[kWave];     // heavy rows by bin, then split rows
+    __shared__ int s_first[kWave], s_cnt[kBins + 2], s_off[kBins + 1], s_task[kBins + 3];
+    __shared__ float s_part[kSmallNnz / kSmallChunk + kWave];  // each row may end with a partly filled chunk
+    const int lane = lane_id(), wid = threadIdx.x / kWave;
+    const int row = lane < kSmallRows ? (int)(blockIdx.x + (long long)lane * gridDim.x) : a.n;
+    int beg = 0, end = 0;
+    if (row < a.n) {
+        beg = a.row_ptr[row];
+        end = a.row_ptr[row + 1];
+    }
+    const int len = end - beg;
+    const bool light = len <= a.threshold;
+    if (wid == 0) {
+        const int bin = light ? -1 : len > a.chunk ? kChunkBin : bin_of(len, a.ipl);
+        int off = 0, task = 0;
+        for (int b = 0; b <= kBins; ++b) {
+            const uint64_t m = __ballot(bin == b);
+            const int cnt = __popcll(m);
+            const int nch = b == kChunkBin && bin == b ? (len + a.chunk - 1) / a.chunk : 0;
+            const int incl = b == kChunkBin && m ? wave_incl_scan(nch) : 0;
+            if (bin == b) {
+                const int k = off + rank_in(m);
+                s_row[k] = row;
+                s_beg[k] = beg;
+                s_end[k] = end;
+                if (b == kChunkBin) s_first[rank_in(m)] = incl - nch;
+            }
+            if (lane == 0) {
+                s_cnt[b] = cnt;
+                s_off[b] = off;
+                s_task[b] = task;
+            }
+            off += cnt;
+            task += b < kBins ? (cnt + (kWave >> b) - 1) / (kWave >> b) : readlane(incl, kWave - 1);
+        }
+        if (lane == 0) s_task[kBins + 1] = task;
+    }
+    __syncthreads();
+    const int total = s_task[kBins + 1];
+    // the last wave sums the light rows first, the others begin with the tasks;
+    // chunks, the longest tasks, come first
+    if (wid == NW - 1 && row < a.n && light) a.y[row] = light_row(a, beg, end);
+    for (int t = total - 1 - wid; t >= 0; t -= NW) {
+        int b = kChunkBin;
+        while (s_task[b] > t) --b;
+        const bool chunk = b == kChunkBin;
+        const int g = chunk ? kWave : 1 << b;
+        const int sub = lane & (g - 1);
+        int first = 0, stop = 0, k = 0;
+        bool ok = true;
+        if (chunk) {
+            const int c = t - s_task[kChunkBin];
+            int i = 0;
+            while (i + 1 < s_cnt[kChunkBin] && s_first[i + 1] <= c) ++i;
+            first = s_beg[s_off[kChunkBin] + i] + (c - s_first[i]) * a.chunk;
+            stop = min(s_end[s_off[kChunkBin] + i], first + a.chunk);
+            first += lane;
+            k = c;
+        } else {
+            const int i = (t - s_task[b]) * (kWave >> b) + (lane >> b);
+            ok = i < s_cnt[b];
+            k = s_off[b] + (ok ? i : 0);
+            if (ok) {
+                first = s_beg[k] + sub;
+                stop = s_end[k];
+            }
+        }
+        float s = dot_strided_u<2 * kUnroll>(a, first, g, stop);
+        s = group_sum(s, g);
+        if (sub == 0) {
+            if (chunk) s_part[k] = s;
+            else if (ok) a.y[s_row[k]] = s;
+        }
+    }
+    if (s_cnt[kChunkBin] == 0) return;  // uniform in the block
+    __syncthreads();
+    for (int i = wid; i < s_cnt[kChunkBin]; i += NW) {
+        const int from = s_first[i];
+        const int to = i + 1 < s_cnt[kChunkBin] ? s_first[i + 1] : total - s_task[kChunkBin];
         Cascade cs;
-        for (int c = lane_id(); c < cnt; c += kWave) cs.add(a.partials[first + c]);
+        for (int c = from + lane; c < to; c += kWave) cs.add(s_part[c]);
         const float s = wave_sum(cs.total());
-        if (lane_id() == 0) a.y[row] = s;
+        if (lane == 0) a.y[s_row[s_off[kChunkBin] + i]] = s;
     }
 }
 
@@ -577,7 +664,7 @@ __global__ __launch_bounds__(kBasicBlock) void spmv_parent_basic(SpmvArgs a)
         const bool heavy = valid && end - beg > a.threshold;
         if (valid && !heavy) a.y[r] = dot_strided(a, beg, 1, end);
         const int s = wave_reserve(heavy, &a.bin_total[0]);
-        if (heavy && s < a.rows_cap) a.rows_buf[s] = make_int4(r, beg, end, 0);
+        if (heavy && s < a.rows_cap) a.basic[s] = make_int4(r, beg, end, 0);
     }
 }
 
@@ -603,24 +690,24 @@ __global__ __launch_bounds__(256) void spmv_gather_hot(SpmvArgs a)
 }
 
 struct SpmvKernels {
-    const void *parent, *classify, *parent_grid, *drain, *combine, *light;
+    const void *parent, *drain, *drain_light;
 };
 
 template <int BLOCK>
 SpmvKernels pick_block(wc_mode mode, bool hot, bool stats)
 {
-    SpmvKernels k{nullptr, reinterpret_cast<const void *>(&spmv_classify<BLOCK>),
-                  stats ? reinterpret_cast<const void *>(&spmv_parent_grid<BLOCK, true>)
-                        : reinterpret_cast<const void *>(&spmv_parent_grid<BLOCK, false>),
-                  hot ? reinterpret_cast<const void *>(&spmv_drain<BLOCK, true>)
-                      : reinterpret_cast<const void *>(&spmv_drain<BLOCK, false>),
-                  reinterpret_cast<const void *>(&spmv_combine<BLOCK>),
-                  reinterpret_cast<const void *>(&spmv_light_rows<BLOCK>)};
+    SpmvKernels k{nullptr,
+                  hot ? reinterpret_cast<const void *>(&spmv_drain<BLOCK, true, false>)
+                      : reinterpret_cast<const void *>(&spmv_drain<BLOCK, false, false>),
+                  reinterpret_cast<const void *>(&spmv_drain<BLOCK, false, true>)};
     switch (mode) {
     case WC_FLAT: k.parent = reinterpret_cast<const void *>(&spmv_parent<WC_FLAT, BLOCK>); break;
     case WC_WAVE: k.parent = reinterpret_cast<const void *>(&spmv_parent<WC_WAVE, BLOCK>); break;
     case WC_BLOCK: k.parent = reinterpret_cast<const void *>(&spmv_parent<WC_BLOCK, BLOCK>); break;
-    default: k.parent = k.parent_grid; break;
+    default:
+        k.parent = stats ? reinterpret_cast<const void *>(&spmv_parent_grid<BLOCK, true>)
+                         : reinterpret_cast<const void *>(&spmv_parent_grid<BLOCK, false>);
+        break;
     }
     return k;
 }
@@ -646,7 +733,8 @@ struct SpmvPlan {
     Config cfg;
     wc_mode mode;
     int grid, dgrid;
-    long long rows_cap, cap, mcap;
+    bool small;  // the whole product in one launch
+    long long rows, basic, cap, mcap;  // entries of the buffers
 };
 
 // Resolves the tune and the launch shapes for a device with `num_cus` compute
@@ -678,8 +766,25 @@ wc_status spmv_shape(int num_cus, const wc_csr *g, const float *val, wc_mode mod
         multi_full = m / spill + 1;
     }
     p->cap = mode != WC_FLAT ? (cfg.buf_capacity > 0 ? std::min(cfg.buf_capacity, cap_full) : cap_full) : 1;
-    p->rows_cap = mode == WC_GRID ? n : 1;
     p->mcap = mode != WC_FLAT ? multi_full : 1;
+    p->basic = cfg.driver == 2 ? n : 0;
+    // A bin holds at most n rows and no more than m / (its shortest length);
+    // bins 2k and 2k + 1 share a region, one from each end, since both together
+    // hold at most n rows.
+    p->rows = 0;
+    long long bin_off[kBins + 1] = {};
+    for (int b = 0; b < kBins && mode == WC_GRID; b += 2) {
+        long long room = 0;
+        for (int k = b; k < std::min(b + 2, kBins); ++k) {
+            const long long shortest =
+                std::max<long long>(cfg.threshold + 1LL, k ? (1LL << (k - 1)) * cfg.items_per_lane + 1 : 1);
+            if (shortest <= ((long long)cfg.items_per_lane << k)) room += m / shortest;
+        }
+        room = std::min(n, room);
+        bin_off[b] = p->rows;
+        p->rows += room;
+        bin_off[b + 1] = p->rows - 1;
+    }
     // wave and block modes launch the parent with a thread per row (one window
     // per workgroup) unless grid_blocks caps it: the hardware hands windows to
     // CUs as they free up, which evens out the windows dense with buffered rows
@@ -693,6 +798,11 @@ wc_status spmv_shape(int num_cus, const wc_csr *g, const float *val, wc_mode mod
     p->dgrid = std::max(1, std::min(cfg.grid, resident));
     SpmvArgs &a = p->a;
     std::memset(&a, 0, sizeof(a));
+    if (mode == WC_GRID) {
+        // steps of more windows once there is one for each of 1024 blocks (four a CU)
+        a.windows = (int)std::min<long long>(kWindows, std::max<long long>(1, windows / 1024));
+        p->grid = (int)std::min<long long>(p->grid, (windows + a.windows - 1) / a.windows);
+    }
     a.row_ptr = g->row_ptr;
     a.col = g->col;
     a.val = val;
@@ -702,22 +812,23 @@ wc_status spmv_shape(int num_cus, const wc_csr *g, const float *val, wc_mode mod
     a.chunk = chunk;
     a.spill = spill;
     a.count_drain = mode == WC_GRID;
-    a.rows_cap = p->rows_cap;
+    std::copy(bin_off, bin_off + kBins + 1, a.bin_off);
+    a.rows_cap = p->basic;
     a.chunk_cap = p->cap;
     a.multi_cap = p->mcap;
     a.want_stats = want_stats;
+    // one launch for a small matrix, where the launch shape, the threshold and
+    // the buffers are the library's choice and nothing is counted
+    p->small = mode == WC_GRID && !hot && !want_stats && !cfg.own_shape && !(tune && tune->threshold > 0) &&
+               cfg.buf_capacity <= 0 && cfg.driver == 0 && m <= kSmallNnz && chunk >= kSmallChunk;
     return WC_OK;
 }
-
-// Rows of the per-parent-block counts and offsets: grid mode's count pass
-// only.
-size_t blk_rows(const SpmvPlan *p) { return p->mode == WC_GRID ? (size_t)p->grid : 1; }
 
 // Bytes of workspace the planned product needs (256-byte aligned pieces).
 size_t spmv_workspace_bytes(const SpmvPlan *p)
 {
-    return 2 * padded(blk_rows(p) * kCols * 4) + padded(kCols * 4) + padded(p->rows_cap * 16) + padded(p->cap * 16) +
-           padded(p->cap * 4) + padded(p->mcap * 16);
+    return padded(kCols * kPad * 4) + padded(p->rows * 4) + padded(p->basic * 16) + padded(p->cap * 16) + padded(p->cap * 4) +
+           padded(p->mcap * 16);
 }
 
 // Lays the workspace out from `base` (256-byte aligned, spmv_workspace_bytes
@@ -731,10 +842,9 @@ char *spmv_carve(SpmvPlan *p, char *base)
         return q;
     };
     SpmvArgs &a = p->a;
-    a.blk_count = reinterpret_cast<int *>(take(blk_rows(p) * kCols * 4));
-    a.blk_off = reinterpret_cast<int *>(take(blk_rows(p) * kCols * 4));
-    a.bin_total = reinterpret_cast<int *>(take(kCols * 4));
-    a.rows_buf = reinterpret_cast<int4 *>(take(p->rows_cap * 16));
+    a.bin_total = reinterpret_cast<int *>(take(kCols * kPad * 4));
+    a.rows_buf = reinterpret_cast<int *>(take(p->rows * 4));
+    a.basic = reinterpret_cast<int4 *>(take(p->basic * 16));
     a.chunks = reinterpret_cast<int4 *>(take(p->cap * 16));
     a.partials = reinterpret_cast<float *>(take(p->cap * 4));
     a.multi = reinterpret_cast<int4 *>(take(p->mcap * 16));
@@ -754,50 +864,43 @@ wc_status spmv_plan(wc_ctx *ctx, const wc_csr *g, const float *val, wc_mode mode
     return WC_OK;
 }
 
-// The kernels of one product (parent; in grid mode classify, scan, parent,
-// drain, combine).
+// Call bracket of the products: the device counters are cleared where something
+// reads them, work counters or the overflow flag (a launch less otherwise).
+wc_status begin_product(wc_ctx *ctx, const SpmvPlan &p, hipStream_t stream, wc_stats *stats)
+{
+    if (stats || p.cfg.fail_on_overflow) return begin_call(ctx, stream, stats);
+    chain_break(ctx);
+    return WC_OK;
+}
+
+// The kernels of one product: the parent, which fills the buffers, and the
+// grid-wide drain of what it put there (flat mode: the parent alone; a small
+// matrix: one kernel).
 wc_status spmv_launch(wc_ctx *ctx, SpmvPlan *p, hipStream_t stream)
 {
     const Config &cfg = p->cfg;
     void *args[] = {&p->a};
+    if (p->small)
+        return launch(ctx, "spmv_small", reinterpret_cast<const void *>(&spmv_small),
+                      dim3((unsigned)((p->a.n + kSmallRows - 1LL) / kSmallRows)), dim3(kSmallBlock), args, stream);
     if (p->mode == WC_FLAT)
         return launch(ctx, "spmv_parent_flat", p->ks.parent, dim3(p->grid), dim3(cfg.block), args, stream);
-    if (p->mode != WC_GRID) {
-        // parent, then the grid-wide drain of the rows it handed on and their combination
-        const char *name = p->mode == WC_WAVE ? "spmv_parent_wave" : "spmv_parent_block";
-        wc_status st = launch(ctx, "spmv_reset", reinterpret_cast<const void *>(&spmv_reset), dim3(1), dim3(kWave),
-                              args, stream);
-        if (st == WC_OK) st = launch(ctx, name, p->ks.parent, dim3(p->grid), dim3(cfg.block), args, stream);
-        if (st == WC_OK) st = launch(ctx, "spmv_drain", p->ks.drain, dim3(p->dgrid), dim3(cfg.block), args, stream);
-        if (st == WC_OK)
-            st = launch(ctx, "spmv_combine", p->ks.combine, dim3(p->dgrid), dim3(cfg.block), args, stream);
-        return st;
-    }
-    int nblocks = p->grid;
-    void *sargs[] = {&p->a, &nblocks};
-    wc_status st = launch(ctx, "spmv_classify", p->ks.classify, dim3(p->grid), dim3(cfg.block), args, stream);
-    if (st == WC_OK)
-        st = launch(ctx, "spmv_scan", reinterpret_cast<const void *>(&spmv_scan), dim3(1), dim3(kCols * kWave), sargs,
-                    stream);
-    if (st == WC_OK)
-        st = launch(ctx, "spmv_parent_grid", p->ks.parent_grid, dim3(p->grid), dim3(cfg.block), args, stream);
+    static const char *const names[] = {"", "spmv_parent_wave", "spmv_parent_block", "spmv_parent_grid"};
+    wc_status st = launch(ctx, "spmv_reset", reinterpret_cast<const void *>(&spmv_reset), dim3(1), dim3(kWave), args,
+                          stream);
+    if (st == WC_OK) st = launch(ctx, names[p->mode], p->ks.parent, dim3(p->grid), dim3(cfg.block), args, stream);
     if (st == WC_OK) st = launch(ctx, "spmv_drain", p->ks.drain, dim3(p->dgrid), dim3(cfg.block), args, stream);
-    if (st == WC_OK) st = launch(ctx, "spmv_combine", p->ks.combine, dim3(p->dgrid), dim3(cfg.block), args, stream);
     return st;
 }
 
 // Grid mode, again on the same matrix with the buffers of the last spmv_launch
 // of this plan still in place (full-size buffers, so nothing overflowed): the
-// rows up to the threshold inline, then the drain and the combination of the
-// reused binned rows and chunks.  Same sums, in the same order, as spmv_launch.
+// drain with the light rows.  Same sums, in the same order, as spmv_launch.
 wc_status spmv_relaunch(wc_ctx *ctx, SpmvPlan *p, hipStream_t stream)
 {
-    const Config &cfg = p->cfg;
+    if (p->small) return spmv_launch(ctx, p, stream);
     void *args[] = {&p->a};
-    wc_status st = launch(ctx, "spmv_light_rows", p->ks.light, dim3(p->grid), dim3(cfg.block), args, stream);
-    if (st == WC_OK) st = launch(ctx, "spmv_drain", p->ks.drain, dim3(p->dgrid), dim3(cfg.block), args, stream);
-    if (st == WC_OK) st = launch(ctx, "spmv_combine", p->ks.combine, dim3(p->dgrid), dim3(cfg.block), args, stream);
-    return st;
+    return launch(ctx, "spmv_drain", p->ks.drain_light, dim3(p->dgrid), dim3(p->cfg.block), args, stream);
 }
 
 // ---------------------------------------------------------------- PageRank
@@ -807,7 +910,9 @@ struct PrArgs {
     float *rank;
     float *contrib;   // rank[u] / outdeg(u), the x of the in-edge sums
     const float *sums;  // sum over the in-edges of v of contrib[u]
-    float *dpart;     // per block of pr_contrib: rank held by vertices without out-edges
+    const float *dpart;  // per block: rank held by vertices without out-edges, of this sweep
+    float *dpart_next;   // ... of the next one
+    int last;            // no sweep follows
     int nparts;
     int n;
     float base;       // (1 - d) / n
@@ -817,38 +922,49 @@ struct PrArgs {
 
 constexpr int kPrBlock = 256;
 
-__global__ __launch_bounds__(kPrBlock) void pr_init(PrArgs p)
+// What vertex u hands to each out-neighbour; the rank of vertices without
+// out-edges goes into dang instead.
+__device__ __forceinline__ float pr_give(const PrArgs &p, int u, float r, Cascade &dang)
 {
-    for (int v = blockIdx.x * kPrBlock + threadIdx.x; v < p.n; v += gridDim.x * kPrBlock) p.rank[v] = p.inv_n;
+    const int od = p.out_degree[u];
+    dang.add(od == 0 ? r : 0.f);
+    return od > 0 ? r / (float)od : 0.f;
 }
 
-// contrib[u] = rank[u] / outdeg(u); the ranks of vertices without out-edges
-// are summed per block in a fixed order into dpart[blockIdx.x].
-__global__ __launch_bounds__(kPrBlock) void pr_contrib(PrArgs p)
+// Before the first sweep: rank 1/n everywhere, its contributions and, in a
+// fixed order, the rank held by each block's vertices without out-edges.
+__global__ __launch_bounds__(kPrBlock) void pr_first(PrArgs p)
 {
     __shared__ float red[kPrBlock / kWave];
     Cascade dang;
     for (int u = blockIdx.x * kPrBlock + threadIdx.x; u < p.n; u += gridDim.x * kPrBlock) {
-        const float r = p.rank[u];
-        const int od = p.out_degree[u];
-        p.contrib[u] = od > 0 ? r / (float)od : 0.f;
-        dang.add(od == 0 ? r : 0.f);
+        if (p.last) p.rank[u] = p.inv_n;  // no sweep follows
+        else p.contrib[u] = pr_give(p, u, p.inv_n, dang);
     }
-    const float dsum_block = block_sum<kPrBlock>(dang.total(), red);
-    if (threadIdx.x == 0) p.dpart[blockIdx.x] = dsum_block;
+    const float held = block_sum<kPrBlock>(dang.total(), red);
+    if (threadIdx.x == 0) p.dpart_next[blockIdx.x] = held;
 }
 
-// rank'[v] = (1 - d) / n + d * (sums[v] + D / n), D the sum of dpart in block
-// order (every block computes the same D).
-__global__ __launch_bounds__(kPrBlock) void pr_update(PrArgs p)
+// The end of a sweep and the start of the next: rank'[v] = (1 - d) / n + d *
+// (sums[v] + D / n), D the sum of dpart in block order (every block computes the
+// same D), and rank's contributions to the next sweep; after the last sweep the
+// rank itself.  The rank of an inner sweep stays in a register.
+__global__ __launch_bounds__(kPrBlock) void pr_step(PrArgs p)
 {
     __shared__ float red[kPrBlock / kWave];
     Cascade part;
     for (int i = threadIdx.x; i < p.nparts; i += kPrBlock) part.add(p.dpart[i]);
     const float dsum = block_sum<kPrBlock>(part.total(), red);
     const float spread = dsum * p.inv_n;
-    for (int v = blockIdx.x * kPrBlock + threadIdx.x; v < p.n; v += gridDim.x * kPrBlock)
-        p.rank[v] = p.base + p.damping * (p.sums[v] + spread);
+    Cascade dang;
+    for (int v = blockIdx.x * kPrBlock + threadIdx.x; v < p.n; v += gridDim.x * kPrBlock) {
+        const float r = p.base + p.damping * (p.sums[v] + spread);
+        if (p.last) p.rank[v] = r;
+        else p.contrib[v] = pr_give(p, v, r, dang);
+    }
+    if (p.last) return;
+    const float held = block_sum<kPrBlock>(dang.total(), red);
+    if (threadIdx.x == 0) p.dpart_next[blockIdx.x] = held;
 }
 
 }  // namespace
@@ -875,7 +991,7 @@ extern "C" wc_status wc_spmv(wc_ctx *ctx, const wc_csr *g, const float *val, con
     p.a.y = y;
     if (p.cfg.driver == 1 || p.cfg.driver == 3 || (p.cfg.driver == 2 && mode != WC_GRID))
         return fail(WC_EINVAL, "wc_spmv: driver 2 needs grid mode; drivers 1 and 3 do not apply");
-    st = begin_call(ctx, stream, stats);
+    st = begin_product(ctx, p, stream, stats);
     if (st != WC_OK) return st;
     if (p.cfg.driver == 2) {
         // Basic dynamic parallelism, emulated: the host reads the heavy rows back
@@ -893,7 +1009,7 @@ extern "C" wc_status wc_spmv(wc_ctx *ctx, const wc_csr *g, const float *val, con
         WC_HIP(hipStreamSynchronize(stream));
         const int count = (int)std::min<long long>(tail, p.a.rows_cap);
         std::vector<int4> rows((size_t)std::max(count, 1));
-        if (count > 0) WC_HIP(hipMemcpy(rows.data(), p.a.rows_buf, sizeof(int4) * (size_t)count, hipMemcpyDeviceToHost));
+        if (count > 0) WC_HIP(hipMemcpy(rows.data(), p.a.basic, sizeof(int4) * (size_t)count, hipMemcpyDeviceToHost));
         chain_break(ctx);
         for (int i = 0; i < count; ++i) {
             int r = rows[i].x, beg = rows[i].y, end = rows[i].z;
@@ -932,7 +1048,7 @@ extern "C" wc_status wc_pagerank(wc_ctx *ctx, const wc_csr *in_graph, const int3
     const long long n = in_graph->n;
     const int pgrid = (int)std::min<long long>((n + kPrBlock - 1) / kPrBlock, 4 * (long long)ctx->num_cus);
     SpmvPlan p;
-    wc_status st = spmv_plan(ctx, in_graph, nullptr, mode, tune, 2 * padded(n * 4) + padded((size_t)pgrid * 4), stream,
+    wc_status st = spmv_plan(ctx, in_graph, nullptr, mode, tune, 2 * padded(n * 4) + 2 * padded((size_t)pgrid * 4), stream,
                              stats, &p);
     if (st != WC_OK) return st;
     if (p.cfg.driver != 0) return fail(WC_EINVAL, "wc_pagerank: only the relaunch driver (driver = 0) applies");
@@ -942,7 +1058,10 @@ extern "C" wc_status wc_pagerank(wc_ctx *ctx, const wc_csr *in_graph, const int3
     q.contrib = pool_take<float>(ctx, n);
     float *sums = pool_take<float>(ctx, n);
     q.sums = sums;
-    q.dpart = pool_take<float>(ctx, pgrid);
+    float *dpart[2] = {pool_take<float>(ctx, pgrid), pool_take<float>(ctx, pgrid)};
+    q.dpart = nullptr;
+    q.dpart_next = dpart[0];
+    q.last = iterations == 0;
     q.nparts = pgrid;
     q.n = (int)n;
     q.base = (float)((1.0 - (double)damping) / (double)n);
@@ -950,22 +1069,23 @@ extern "C" wc_status wc_pagerank(wc_ctx *ctx, const wc_csr *in_graph, const int3
     q.inv_n = (float)(1.0 / (double)n);
     p.a.x = q.contrib;
     p.a.y = sums;
-    st = begin_call(ctx, stream, stats);
+    st = begin_product(ctx, p, stream, stats);
     if (st != WC_OK) return st;
     void *args[] = {&q};
-    st = launch(ctx, "pr_init", reinterpret_cast<const void *>(&pr_init), dim3(pgrid), dim3(kPrBlock), args, stream);
+    st = launch(ctx, "pr_first", reinterpret_cast<const void *>(&pr_first), dim3(pgrid), dim3(kPrBlock), args, stream);
     // grid mode: the in-edge structure is the same every sweep, so the binned
     // rows and chunks of the first sweep serve the later ones (only when the
     // buffers are full size, so that nothing overflowed, and without work
     // counters, which count each sweep's binning)
     const bool reuse = mode == WC_GRID && !stats && !(tune && tune->buf_capacity > 0);
     for (int it = 0; it < iterations && st == WC_OK; ++it) {
-        st = launch(ctx, "pr_contrib", reinterpret_cast<const void *>(&pr_contrib), dim3(pgrid), dim3(kPrBlock), args,
-                    stream);
-        if (st == WC_OK) st = reuse && it > 0 ? spmv_relaunch(ctx, &p, stream) : spmv_launch(ctx, &p, stream);
+        st = reuse && it > 0 ? spmv_relaunch(ctx, &p, stream) : spmv_launch(ctx, &p, stream);
+        q.dpart = dpart[it & 1];
+        q.dpart_next = dpart[(it + 1) & 1];
+        q.last = it + 1 == iterations;
         if (st == WC_OK)
-            st = launch(ctx, "pr_update", reinterpret_cast<const void *>(&pr_update), dim3(pgrid), dim3(kPrBlock),
-                        args, stream);
+            st = launch(ctx, "pr_step", reinterpret_cast<const void *>(&pr_step), dim3(pgrid), dim3(kPrBlock), args,
+                        stream);
     }
     if (st != WC_OK) return st;
     return end_call(ctx, stream, stats, iterations, p.cfg.fail_on_overflow);
@@ -1064,7 +1184,7 @@ extern "C" wc_status wc_spmv_hot(wc_ctx *ctx, const wc_csr *a_hot, int32_t hot, 
     p.a.hot = hot;
     p.a.hot_ids = hot_ids;
     p.a.x_hot = pool_take<float>(ctx, (size_t)std::max(hot, 1));
-    st = begin_call(ctx, stream, stats);
+    st = begin_product(ctx, p, stream, stats);
     if (st != WC_OK) return st;
     if (hot > 0) {
         void *args[] = {&p.a};
@@ -1100,14 +1220,18 @@ struct NoAllocDevice {
 std::mutex g_noalloc_mu;
 NoAllocDevice g_noalloc[kMaxDevices];
 
-// Workspace bound from n, m and the tune alone (the parent grid at its
-// largest, ceil(n / block)), so oversized calls are refused before any HIP
-// call is made.
+// Workspace bound from n, m and the tune alone (the documented one, in grid mode
+// an upper bound of what the kernels use but for a few bytes), so oversized
+// calls are refused before any HIP call is made.
 size_t spmv_noalloc_bound(const wc_csr *g, const SpmvPlan *p)
 {
-    SpmvPlan q = *p;
-    q.grid = (int)std::max<long long>(1, ((long long)g->n + q.cfg.block - 1) / q.cfg.block);
-    return spmv_workspace_bytes(&q) + padded(sizeof(DevStats));
+    size_t bytes = spmv_workspace_bytes(p);
+    if (p->mode == WC_GRID) {
+        const size_t n = (size_t)g->n, blocks = (n + p->cfg.block - 1) / p->cfg.block;
+        bytes = std::max(bytes, 2 * padded(n * 16) + padded(p->cap * 16) + padded(p->cap * 4) +
+                                    2 * padded(blocks * 36) + padded(36));
+    }
+    return bytes + padded(sizeof(DevStats));
 }
 
 }  // namespace
