@@ -27,7 +27,8 @@
 //           moldable grid after the kernel boundary, one wave per chunk.  The
 //           thread that readies a vertex buffers its range right away, so the
 //           drain of round r is also the parent of round r + 1: one kernel
-//           per round.
+//           per round, and for consecutive small rounds one workgroup in one
+//           kernel (color_narrow).
 //   flat  - every vertex walks all of its neighbours itself.
 // Outside grid mode `threshold` applies in the count pass and the rounds
 // alike; in grid mode it applies to the count pass, and every readied
@@ -63,6 +64,7 @@ struct ColorArgs {
     int4 *chunks1;    // grid: the chunks of odd rounds
     long long chunk_cap;
     int *colored;     // grid: vertices colored so far
+    int *state;       // grid with narrow rounds: see color_narrow
     int n;
     int threshold;
     int chunk;
@@ -328,19 +330,28 @@ __global__ __launch_bounds__(BLOCK) void color_round_drain(ColorArgs a, int r)
     if (a.want_stats) stat_flush(a.stats, acc);
 }
 
+// Where color_narrow left off (ColorArgs::state).
+enum { kRound = 0, kWide = 1, kDone = 2, kStateInts = 3 };
+
 // Round r in grid mode: one wave per buffered chunk (a readied vertex's
 // neighbour range, buffered while round r - 1 ran), then one lane per vertex
 // the buffer could not take.  Vertices readied here buffer their ranges for
-// round r + 1.
+// round r + 1.  r < 0: the round that color_narrow found too large for itself,
+// if it did.
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) void color_round_grid(ColorArgs a, int r)
 {
+    const bool narrow = r < 0;
+    if (narrow) {
+        if (!a.state[kWide]) return;
+        r = a.state[kRound];
+    }
     const int nchunks = a.chunk_tail[(r % 3) * kPad];
     const int ndefer = a.qtail[(r % 3) * kPad];
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         a.chunk_tail[((r + 2) % 3) * kPad] = 0;
         a.qtail[((r + 2) % 3) * kPad] = 0;
-        publish_host(a.host_ring, r % kHostRing, a.stats, (nchunks != 0 || ndefer != 0) ? 1 : 0);
+        if (!narrow) publish_host(a.host_ring, r % kHostRing, a.stats, (nchunks != 0 || ndefer != 0) ? 1 : 0);
     }
     if (nchunks == 0 && ndefer == 0) return;
     const int total = (long long)nchunks < a.chunk_cap ? nchunks : (int)a.chunk_cap;
@@ -374,6 +385,231 @@ __global__ __launch_bounds__(BLOCK) void color_round_grid(ColorArgs a, int r)
     if (a.want_stats) stat_flush(a.stats, acc);
 }
 
+// Consecutive small rounds of grid mode in one launch, by one workgroup: the
+// grid-wide barrier between rounds is its own barrier.  Most rounds color a few
+// dozen vertices and release some thousand edges (scale-16 graph, 775 rounds: 50
+// vertices, 4,200 entries in 74 chunks at the median), less than a launch's
+// worth.  The round's chunks are listed in LDS; a wave takes one, two or four of
+// them at a time, and sixteen lanes list the chunks of a vertex readied here.
+// The counts are kept in LDS too, 16 bits each, for the launch.  Bound by the
+// round's two round trips to memory (entries, the readied vertices' ranges) and,
+// beyond some thousand entries, by what one CU's LDS and issue slots take.
+// Scale-16 graph, 65,536 vertices and 3.4M entries: 3.9 us a round against 6.5 of
+// a launch, 5,200 -> 3,150 us in all; 1,024 and 4,096 vertices 508 and 1,043 ->
+// 180 and 364 us.  Entries side by side over the threads, each finding its range
+// by a search over prefixes: 5.7 us a round; the counts in memory: 6.9.
+// Rule: graphs of up to kNarrowN vertices, whose counts LDS holds, and rounds of
+// up to kNarrowChunks chunks (at 128, 3,300 instead of 2,450 us on 65,536
+// vertices of 16 edges; at 512 the same).
+// The workgroup starts from, and where a round is larger than it takes leaves,
+// the chunk buffer of the round: color_round_grid does that round
+// (state[kWide]), and the next launch goes on after it.  A launch ends after
+// kNarrowRounds rounds at the latest.  Each launch publishes the number of
+// colored vertices when all is done, -1 when not, and kNarrowBad when a count
+// would go below zero: the graph is not symmetric, packed counts would spill over
+// into their neighbours, and the call is done again without this kernel.
+constexpr int kNarrowBlock = 1024;
+constexpr int kNarrowGroup = 16;     // lanes that list one vertex's chunks
+constexpr int kNarrowList = 1024;    // chunks that a list holds
+constexpr int kNarrowChunks = 256;   // chunks of a round that is taken here
+constexpr int kNarrowChunk = 2 * kWave;  // largest chunk
+constexpr int kNarrowRounds = 4096;
+constexpr int kNarrowN = 65536;
+constexpr int kNarrowBad = -2;
+// The entries of a round's chunks, U chunks a wave at a time: releases, and the
+// vertices that they ready into s_ready (beyond it: a.queue0).  Each step for all
+// entries before the next: a round trip a step, not one an entry.  True on a
+// thread that found a count at zero.
+template <int U>
+__device__ __forceinline__ bool narrow_entries(const ColorArgs &a, const int2 *list, int count, int wid,
+                                               unsigned int *s_wait, int *s_found, int *s_ready)
+{
+    constexpr int NW = kNarrowBlock / kWave;
+    const int lane = lane_id();
+    bool bad = false;
+    for (int i0 = wid; i0 < count; i0 += NW * U) {
+        int w[2 * U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = i0 + u * NW;
+            const int2 d = i < count ? list[i] : make_int2(0, 0);
+            const int e = d.x + lane;
+            w[2 * u] = e < d.y ? a.rcol[e] : kNoRelease;
+            w[2 * u + 1] = e + kWave < d.y ? a.rcol[e + kWave] : kNoRelease;
+        }
+        unsigned int old[2 * U];
+#pragma unroll
+        for (int u = 0; u < 2 * U; ++u)
+            old[u] = w[u] >= 0 ? atomicSub(&s_wait[w[u] >> 1], 1u << 16 * (w[u] & 1)) : 0x20002u;
+        int ready = 0;  // of this thread: one reservation
+#pragma unroll
+        for (int u = 0; u < 2 * U; ++u) {
+            old[u] = old[u] >> 16 * (w[u] & 1) & 0xffffu;
+            bad |= old[u] == 0;
+            ready += old[u] == 1 ? 1 : 0;
+        }
+        if (ready) {
+            int q = atomicAdd(s_found, ready);
+#pragma unroll
+            for (int u = 0; u < 2 * U; ++u)
+                if (old[u] == 1) {
+                    if (q < kNarrowBlock) s_ready[q] = w[u];
+                    else if (q - kNarrowBlock < a.n) a.queue0[q - kNarrowBlock] = w[u];
+                    ++q;
+                }
+        }
+    }
+    return bad;
+}
+
+__global__ __launch_bounds__(kNarrowBlock) void color_narrow(ColorArgs a, int step)
+{
+    constexpr int NW = kNarrowBlock / kWave;
+    __shared__ int2 s_list[2][kNarrowList];
+    __shared__ int s_ready[kNarrowBlock];
+    __shared__ int s_next[2], s_found[2];  // chunks of a list, vertices readied
+    __shared__ int s_tmp[2 * NW], s_readied, s_spill, s_bad;
+    __shared__ unsigned int s_wait[kNarrowN / 2];
+    const int tid = threadIdx.x, lane = lane_id();
+    const int wid = __builtin_amdgcn_readfirstlane(tid / kWave);
+    if (a.state[kDone]) {
+        if (tid == 0) publish_host(a.host_ring, step % kHostRing, a.stats, *a.colored);
+        return;
+    }
+    int r = a.state[kRound] + a.state[kWide];  // the wide round, if there was one, is done
+    const int nchunks = a.chunk_tail[(r % 3) * kPad], ndefer = a.qtail[(r % 3) * kPad];
+    bool fits = ndefer == 0 && nchunks <= kNarrowChunks;
+    int k = 0;  // rounds done here; the list of the current one is k & 1
+    if (tid == 0) {
+        s_next[0] = fits ? nchunks : 0;
+        s_found[0] = s_readied = s_spill = s_bad = 0;
+    }
+    if (fits && nchunks > 0) {
+        bool large = false;
+        for (int i = tid; 2 * i < a.n; i += kNarrowBlock) {
+            const unsigned int lo = (unsigned int)a.wait[2 * i];
+            const unsigned int hi = 2 * i + 1 < a.n ? (unsigned int)a.wait[2 * i + 1] : 0u;
+            large |= (lo | hi) > 0xffffu;
+            s_wait[i] = lo | hi << 16;
+        }
+        if (tid < nchunks) {
+            const int4 d = ((r & 1) ? a.chunks1 : a.chunks)[tid];
+            s_list[0][tid] = make_int2(d.y, d.z);
+        }
+        if (__syncthreads_or(large ? 1 : 0)) fits = false;  // multi-edges: more than 16 bits count
+    }
+    __syncthreads();
+    int readied = 0;
+    bool below_zero = false;
+    for (; fits && k < kNarrowRounds; ++k, ++r) {
+        const int count = s_next[k & 1];
+        if (count == 0 || count > kNarrowChunks) break;
+        // the entries: releases, and the vertices that they ready
+        if (tid == 0) s_next[(k + 1) & 1] = 0;
+        bool bad = false;
+        // more chunks a wave at once only where it has them: unused places cost issue slots
+        if (count <= NW) bad |= narrow_entries<1>(a, s_list[k & 1], count, wid, s_wait, &s_found[k & 1], s_ready);
+        else if (count <= 2 * NW) bad |= narrow_entries<2>(a, s_list[k & 1], count, wid, s_wait, &s_found[k & 1], s_ready);
+        else bad |= narrow_entries<4>(a, s_list[k & 1], count, wid, s_wait, &s_found[k & 1], s_ready);
+        if (bad) s_bad = 1;
+        __syncthreads();
+        // the vertices: their color, and their chunks into the next list
+        const int found = s_found[k & 1];
+        const bool stop = s_bad;  // set before the round's first barrier, read before its second
+        if (tid == 0) s_found[(k + 1) & 1] = 0;
+        int2 *next = s_list[(k + 1) & 1];
+        const int sub = lane & (kNarrowGroup - 1);
+        for (int i = tid / kNarrowGroup; i < found; i += kNarrowBlock / kNarrowGroup) {
+            const int v = i < kNarrowBlock ? s_ready[i] : a.queue0[min(i - kNarrowBlock, a.n - 1)];
+            const int beg = a.row_ptr[v], end = a.row_ptr[v + 1];
+            const int nch = (end - beg + kNarrowChunk - 1) / kNarrowChunk;
+            int slot = 0;
+            if (sub == 0) {
+                a.color[v] = r + 1;
+                ++readied;
+                slot = atomicAdd(&s_next[(k + 1) & 1], nch);
+            }
+            slot = __shfl(slot, lane & ~(kNarrowGroup - 1), kWave);
+            if (slot + nch <= kNarrowList) {
+                for (int c = sub; c < nch; c += kNarrowGroup) {
+                    const int b = beg + c * kNarrowChunk;
+                    next[slot + c] = make_int2(b, min(end, b + kNarrowChunk));
+                }
+            } else {
+                // more than the list holds (the round is too large anyway): the vertex
+                // to memory, empty entries in its place
+                for (int c = slot + sub; c < kNarrowList; c += kNarrowGroup) next[c] = make_int2(0, 0);
+                if (sub == 0) {
+                    const int q = atomicAdd(&s_spill, 1);
+                    if (q < a.n) a.queue1[q] = v;
+                }
+            }
+        }
+        __syncthreads();
+        if (stop) {
+            below_zero = true;
+            break;
+        }
+    }
+    readied = wave_sum_i(readied);
+    if (lane == 0 && readied) atomicAdd(&s_readied, readied);
+    if (below_zero) {
+        // the launches behind this one find nothing to do
+        if (tid == 0) {
+            *a.colored = kNarrowBad;
+            a.state[kWide] = 0;
+            a.state[kDone] = 1;
+            publish_host(a.host_ring, step % kHostRing, a.stats, kNarrowBad);
+        }
+        return;
+    }
+    const int count = s_next[k & 1];
+    const bool done = fits && count == 0;
+    int chunks = 0;
+    if (k > 0 && !done) {
+        for (int i = tid; 2 * i < a.n; i += kNarrowBlock) {
+            const unsigned int q = s_wait[i];
+            a.wait[2 * i] = (int)(q & 0xffffu);
+            if (2 * i + 1 < a.n) a.wait[2 * i + 1] = (int)(q >> 16);
+        }
+        // the list becomes the chunk buffer of its round
+        int4 *out = (r & 1) ? a.chunks1 : a.chunks;
+        chunks = min(count, kNarrowList);
+        if (tid < chunks) out[tid] = make_int4(0, s_list[k & 1][tid].x, s_list[k & 1][tid].y, 0);
+        const int spilled = min(s_spill, a.n);
+        for (int i0 = 0; i0 < spilled; i0 += kNarrowBlock) {
+            int beg = 0, end = 0;
+            if (i0 + tid < spilled) {
+                const int v = a.queue1[i0 + tid];
+                beg = a.row_ptr[v];
+                end = a.row_ptr[v + 1];
+            }
+            const int nch = (end - beg + a.chunk - 1) / a.chunk;
+            int at, unused, tot, unused2;
+            block_scan2<kNarrowBlock>(nch, 0, s_tmp, at, unused, tot, unused2);
+            for (int c = 0; c < nch; ++c) {
+                const int cb = beg + c * a.chunk;
+                out[chunks + at + c] = make_int4(0, cb, min(end, cb + a.chunk), 0);
+            }
+            chunks += tot;
+        }
+    }
+    __syncthreads();
+    if (tid != 0) return;
+    if (k > 0 && !done) {
+        a.chunk_tail[(r % 3) * kPad] = chunks;
+        a.chunk_tail[((r + 1) % 3) * kPad] = 0;
+        a.qtail[(r % 3) * kPad] = 0;
+        a.qtail[((r + 1) % 3) * kPad] = 0;
+    }
+    const int colored = *a.colored + s_readied;
+    *a.colored = colored;
+    a.state[kRound] = r;
+    a.state[kWide] = !done && !(fits && k == kNarrowRounds);
+    a.state[kDone] = done;
+    publish_host(a.host_ring, step % kHostRing, a.stats, done ? colored : -1);
+}
+
 // Clears the rings before the count pass appends to the first queue.
 __global__ void color_reset(ColorArgs a)
 {
@@ -382,6 +618,7 @@ __global__ void color_reset(ColorArgs a)
         a.chunk_tail[threadIdx.x * kPad] = 0;
     }
     if (threadIdx.x == 0) *a.colored = 0;
+    if (threadIdx.x < kStateInts) a.state[threadIdx.x] = 0;
 }
 
 // Grid mode: hands the number of colored vertices to the host.
@@ -674,7 +911,7 @@ extern "C" wc_status wc_color(wc_ctx *ctx, const wc_csr *g, const uint32_t *prio
     const bool spills = mode == WC_WAVE || mode == WC_BLOCK;
     const long long cap_full = grid_mode ? n + m / chunk + 1 : spills ? 2 * (m / chunk) + 1 : 1;
     const long long cap = cfg.buf_capacity > 0 && mode != WC_FLAT ? std::min(cfg.buf_capacity, cap_full) : cap_full;
-    const size_t need = 3 * padded(n * 4) + padded(m * 4) + 3 * padded(3 * kPad * 4) +
+    const size_t need = 3 * padded(n * 4) + padded(m * 4) + 4 * padded(3 * kPad * 4) +
                         (grid_mode ? 2 : 1) * padded(cap * 16);
     st = pool_reserve(ctx, need, stream);
     if (st != WC_OK) return st;
@@ -694,6 +931,7 @@ extern "C" wc_status wc_color(wc_ctx *ctx, const wc_csr *g, const uint32_t *prio
     a.chunks1 = grid_mode ? pool_take<int4>(ctx, cap) : nullptr;
     a.chunk_cap = cap;
     a.colored = pool_take<int>(ctx, 3 * kPad);
+    a.state = pool_take<int>(ctx, 3 * kPad);
     a.n = (int)n;
     a.threshold = cfg.threshold;
     a.chunk = chunk;
@@ -704,19 +942,22 @@ extern "C" wc_status wc_color(wc_ctx *ctx, const wc_csr *g, const uint32_t *prio
     const int dgrid = std::max(1, std::min(cfg.grid, resident));
     st = begin_call(ctx, stream, stats);
     if (st != WC_OK) return st;
-    {
+    // the counts and round 0
+    auto start = [&]() -> wc_status {
         void *args[] = {&a};
-        st = launch(ctx, "color_reset", reinterpret_cast<const void *>(&color_reset), dim3(1), dim3(64), args,
-                    stream);
-        if (st == WC_OK) st = launch(ctx, "color_count", ks.count, dim3(grid), dim3(cfg.block), args, stream);
-        if (st == WC_OK && mode != WC_FLAT)
-            st = launch(ctx, "color_count_drain", ks.count_drain, dim3(dgrid), dim3(cfg.block), args, stream);
+        wc_status s = launch(ctx, "color_reset", reinterpret_cast<const void *>(&color_reset), dim3(1), dim3(64), args,
+                             stream);
+        if (s == WC_OK) s = launch(ctx, "color_count", ks.count, dim3(grid), dim3(cfg.block), args, stream);
+        if (s == WC_OK && mode != WC_FLAT)
+            s = launch(ctx, "color_count_drain", ks.count_drain, dim3(dgrid), dim3(cfg.block), args, stream);
         const int sg = (int)std::min<long long>((n + kSeedBlock - 1) / kSeedBlock, 4096);
         const void *seed = grid_mode ? reinterpret_cast<const void *>(&color_seed<true>)
                                      : reinterpret_cast<const void *>(&color_seed<false>);
-        if (st == WC_OK) st = launch(ctx, "color_seed", seed, dim3(sg), dim3(kSeedBlock), args, stream);
-        if (st != WC_OK) return st;
-    }
+        if (s == WC_OK) s = launch(ctx, "color_seed", seed, dim3(sg), dim3(kSeedBlock), args, stream);
+        return s;
+    };
+    st = start();
+    if (st != WC_OK) return st;
     static const char *names[] = {"color_round_flat", "color_round_wave", "color_round_block", "color_round_grid"};
     // relaunch driver: rounds kept in flight (each publishes whether it has
     // work: its queue size, or in grid mode whether chunks or vertices wait);
@@ -724,7 +965,42 @@ extern "C" wc_status wc_color(wc_ctx *ctx, const wc_csr *g, const uint32_t *prio
     const int window = 4;
     int rounds = 0, launched = 0;
     long long colored = 0;
-    for (;;) {
+    // Grid mode, the launch shape, threshold and buffers the library's choice and
+    // nothing counted per round: small rounds by one workgroup, many a launch,
+    // and a grid-wide launch where a round is too large for it.
+    bool narrow = grid_mode && n <= kNarrowN && chunk <= kNarrowChunk && !stats && !cfg.own_shape && !(tune && tune->threshold > 0) &&
+                  cfg.buf_capacity <= 0;
+    while (narrow) {
+        while (launched < rounds + window) {
+            clear_round_slot(ctx, launched);
+            void *nargs[] = {&a, &launched};
+            st = launch(ctx, "color_narrow", reinterpret_cast<const void *>(&color_narrow), dim3(1),
+                        dim3(kNarrowBlock), nargs, stream);
+            int by_state = -1;
+            void *args[] = {&a, &by_state};
+            if (st == WC_OK) st = launch(ctx, names[mode], ks.round, dim3(dgrid), dim3(cfg.block), args, stream);
+            if (st != WC_OK) return st;
+            ++launched;
+        }
+        int c = 0;
+        st = wait_round_count(ctx, rounds, &c);
+        if (st != WC_OK) return st;
+        if (c >= 0) {
+            colored = c;
+            break;
+        }
+        if (c == kNarrowBad) {
+            // what is enqueued behind that launch does nothing
+            st = begin_call(ctx, stream, stats);
+            if (st == WC_OK) st = start();
+            if (st != WC_OK) return st;
+            rounds = launched = 0;
+            narrow = false;
+            break;
+        }
+        if (++rounds > n + 1) return fail(WC_ETIMEOUT, "wc_color: more rounds than vertices");
+    }
+    while (!narrow) {
         while (launched < rounds + window) {
             clear_round_slot(ctx, launched);
             void *args[] = {&a, &launched};
@@ -743,7 +1019,7 @@ extern "C" wc_status wc_color(wc_ctx *ctx, const wc_csr *g, const uint32_t *prio
         if (!grid_mode && colored > n) return fail(WC_EINVAL, "wc_color: more queued vertices than vertices");
         if (rounds > n + 1) return fail(WC_ETIMEOUT, "wc_color: more rounds than vertices");
     }
-    if (grid_mode) {
+    if (grid_mode && !narrow) {
         // the last round with work colored the vertices of the largest color;
         // a graph without edges has one color and no round with work
         rounds = std::max(rounds, 1);
