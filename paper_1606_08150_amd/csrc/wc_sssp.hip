@@ -23,7 +23,8 @@
 // stamp; grid mode keeps relaxed_at[v], the distance v's edges were last
 // relaxed with, and its frontier is every vertex whose distance is below it.
 // The distances reached are the unique shortest-path distances, so every mode
-// and schedule yields identical results.
+// and schedule yields identical results.  Grid mode runs a small graph in one
+// workgroup (sssp_small).
 #include <cstring>
 #include <algorithm>
 #include <vector>
@@ -653,6 +654,133 @@ __global__ __launch_bounds__(BLOCK) void sssp_drain(SsspArgs a, int r)
     }
 }
 
+// ---- small graphs -------------------------------------------------------------------------------
+
+// A whole call of grid mode by one workgroup, for graphs whose distances, last
+// relaxed distances and row ranges LDS holds: the grid-wide barrier of a round is
+// the workgroup's own.  A round lists the vertices whose distance is below the
+// one their edges were last relaxed with, by the lanes their edges ask for
+// (4 lanes, 16 lanes, a wave), then relaxes them, four edges a lane and step,
+// with LDS atomics.  A launch costs about 4 us and a round of the general path
+// two, so a graph of a few thousand vertices was all launches.  Bound by what one
+// CU issues for its edges (about 0.2 us per thousand edges relaxed).  Power-law
+// graphs of 16 edges a vertex, general path -> this: shortest paths 1,024 vertices
+// 148 -> 29 us, 2,048 168 -> 51, 4,096 175 -> 78, 8,192 192 -> 158; levels 1,024
+// vertices 90 -> 13 us, 4,096 97 -> 34.  One edge a lane and load instead of four
+// consecutive ones: 35, 62, 95 and 217 us.  Half or twice the lanes a vertex: 0 to
+// 10 % slower.
+//
+// The limits: LDS ends at 8,192 vertices (16 bytes each), and there a graph of 16
+// edges a vertex (131,072) is still ahead; more edges would pass the general path,
+// which has the whole device for them.
+constexpr int kSmallBlock = 1024;
+constexpr int kSmallN = 8192;
+constexpr int kSmallM = 1 << 17;
+constexpr int kSmallLightLanes = 4;  // lanes of a vertex of up to kSmallLight edges
+constexpr int kSmallLight = 32;
+constexpr int kSmallMidLanes = 16;   // ... of up to kSmallMid edges; beyond, a wave
+constexpr int kSmallMid = 256;
+
+struct Quad {
+    int x[4];  // aligned to 4 bytes: a row starts anywhere
+};
+
+// The edges [e, end) of a vertex at distance du by a group of lanes: four
+// consecutive edges a lane and step (e: the lane's first), so that a row costs a
+// quarter of the loads. A quad never passes the end of the array (m >= 4).
+__device__ __forceinline__ void relax_small(const SsspArgs &a, int m, int e, int end, int stride, uint32_t du,
+                                            uint32_t *dist)
+{
+    while (__any(e < end)) {
+        if (e < end) {
+            const int q = min(e, m - 4);
+            const Quad v = *reinterpret_cast<const Quad *>(a.col + q);
+            Quad w = {{1, 1, 1, 1}};
+            if (a.w) w = *reinterpret_cast<const Quad *>(a.w + q);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                if (q + k < e || q + k >= end) continue;
+                const uint32_t nd = add_sat(du, static_cast<uint32_t>(w.x[k]));
+                if (nd < dist[v.x[k]]) atomicMin(&dist[v.x[k]], nd);
+            }
+        }
+        e += 4 * stride;
+    }
+}
+
+__global__ __launch_bounds__(kSmallBlock) void sssp_small(SsspArgs a, int m, int src)
+{
+    __shared__ uint32_t s_dist[kSmallN], s_at[kSmallN];
+    __shared__ int s_ptr[kSmallN + 1], s_list[kSmallN], s_long[kSmallM / kSmallMid], s_count[2][3];
+    const int tid = threadIdx.x, lane = lane_id();
+    const int wid = __builtin_amdgcn_readfirstlane(tid / kWave);
+    for (int v = tid; v < a.n; v += kSmallBlock) {
+        s_dist[v] = v == src ? 0u : kInf;
+        s_at[v] = kInf;
+        s_ptr[v] = a.row_ptr[v];
+    }
+    if (tid == 0) s_ptr[a.n] = a.row_ptr[a.n];
+    if (tid < 6) (&s_count[0][0])[tid] = 0;
+    __syncthreads();
+    for (int r = 0;; r ^= 1) {
+        // light vertices from the front of the list, middling ones from its end,
+        // long ones (at most kSmallM / kSmallMid) in a list of their own
+        for (int v0 = 0; v0 < a.n; v0 += kSmallBlock) {
+            const int v = v0 + tid;
+            int kind = -1;
+            if (v < a.n) {
+                const uint32_t d = s_dist[v];
+                if (d < s_at[v]) {
+                    s_at[v] = d;
+                    const int deg = s_ptr[v + 1] - s_ptr[v];
+                    kind = deg <= 0 ? -1 : deg <= kSmallLight ? 0 : deg <= kSmallMid ? 1 : 2;
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                const uint64_t m = __ballot(kind == k);
+                if (!m) continue;
+                int base = 0;
+                if (lane == 0) base = atomicAdd(&s_count[r][k], __builtin_popcountll(m));
+                base = readlane(base, 0);
+                if (kind == k) {
+                    const int i = base + rank_in(m);
+                    if (k == 0) s_list[i] = v;
+                    else if (k == 1) s_list[kSmallN - 1 - i] = v;
+                    else s_long[i] = v;
+                }
+            }
+        }
+        __syncthreads();
+        const int light = s_count[r][0], mid = s_count[r][1], lng = s_count[r][2];
+        if (tid < 3) s_count[r ^ 1][tid] = 0;
+        if (light + mid + lng == 0) break;
+        // a wave's tasks: a long vertex, 64 / kSmallMidLanes middling ones or 64 /
+        // kSmallLightLanes light ones, the long ones first
+        constexpr int kMidTask = kWave / kSmallMidLanes, kLightTask = kWave / kSmallLightLanes;
+        const int mid0 = lng, light0 = mid0 + (mid + kMidTask - 1) / kMidTask;
+        const int tasks = light0 + (light + kLightTask - 1) / kLightTask;
+        for (int t = wid; t < tasks; t += kSmallBlock / kWave) {
+            const int kind = t < mid0 ? 2 : t < light0 ? 1 : 0;
+            const int g = kind == 2 ? kWave : kind == 1 ? kSmallMidLanes : kSmallLightLanes;
+            int u = -1;
+            if (kind == 2) {
+                u = s_long[t];
+            } else if (kind == 1) {
+                const int i = (t - mid0) * kMidTask + lane / kSmallMidLanes;
+                if (i < mid) u = s_list[kSmallN - 1 - i];
+            } else {
+                const int i = (t - light0) * kLightTask + lane / kSmallLightLanes;
+                if (i < light) u = s_list[i];
+            }
+            const int sub = lane & (g - 1);
+            relax_small(a, m, u >= 0 ? s_ptr[u] + 4 * sub : 0, u >= 0 ? s_ptr[u + 1] : 0, g, u >= 0 ? s_at[u] : 0u, s_dist);
+        }
+        __syncthreads();
+    }
+    for (int v = tid; v < a.n; v += kSmallBlock) a.dist[v] = s_dist[v];
+}
+
 // basic dynamic parallelism, emulated for comparison (driver 2): the child of
 // ONE buffered vertex, thread-mapped over its edges, launched per vertex by
 // the host.  Same relaxation as the drain.
@@ -809,6 +937,16 @@ wc_status run_sssp(wc_ctx *ctx, const wc_csr *g, const uint32_t *w, int32_t src,
     if ((mode == WC_WAVE || mode == WC_BLOCK) && cfg.buffer_alloc == 0)
         grid = std::max(1, own_grid ? std::min(cfg.grid, windows) : windows);
     const int dgrid = std::max(1, std::min(cfg.grid, resident));
+    // a small graph in one launch, where the tune is the library's choice, nothing
+    // is counted and the stages need no times of their own (its loads take four
+    // edges, so there have to be four)
+    if (mode == WC_GRID && n <= kSmallN && m >= 4 && m <= kSmallM && cfg.driver == 0 && !stats && !ctx->timing &&
+        !cfg.own_shape && !(tune && (tune->threshold > 0 || tune->buf_capacity > 0))) {
+        int edges = static_cast<int>(m);
+        void *args[] = {&a, &edges, &src};
+        return launch(ctx, "sssp_small", reinterpret_cast<const void *>(&sssp_small), dim3(1), dim3(kSmallBlock), args,
+                      stream);
+    }
     st = begin_call(ctx, stream, stats);
     if (st != WC_OK) return st;
     int init_grid = (int)std::min<long long>((n + 255) / 256, 4096);
