@@ -24,7 +24,6 @@ namespace wc {
 namespace {
 
 constexpr int kPad = 32;
-constexpr int kUnroll = 4;
 constexpr int kWinInst = 256;  // vertices per entry of the instance lookup table
 
 struct Inst {
@@ -37,7 +36,7 @@ struct Inst {
     int threshold;
     int chunk;
     int src;
-    int pad;
+    int m;
 };
 
 struct BatchArgs {
@@ -46,7 +45,8 @@ struct BatchArgs {
     const int *win_inst;  // [total / kWinInst + 1]: instance owning vertex k * kWinInst
     int count;
     int total;         // vbase[count]
-    int *stamp;        // [total]
+    uint16_t *mark;    // [total]: the round whose frontier the vertex is in (its low 8 bits: one of an
+                       // earlier round has nothing left to relax) << 8 | bound_code of its distance
     uint32_t *relaxed_at;  // [total]: the largest distance the vertex's edges were last relaxed with
     int *active;       // ring of 3 (stride kPad)
     int *chunk_tail;   // ring of 3 (stride kPad)
@@ -73,36 +73,108 @@ __device__ __forceinline__ uint32_t add_sat(uint32_t du, uint32_t w)
     return s < du ? kInf : s;
 }
 
-__device__ __forceinline__ bool relax_loaded(uint32_t *dist, int *stamp_base, int v, uint32_t nd, uint32_t dv,
-                                             int next)
+// The edge range of a frontier vertex, its instance's arrays along with it.
+struct Range {
+    gptr<const int> col;
+    gptr<const uint32_t> w;
+    gptr<uint32_t> dist;
+    gptr<uint16_t> mark;
+    int beg, end;
+    uint32_t du;
+    int m;  // edges of the instance
+};
+
+__device__ __forceinline__ Range make_range(const BatchArgs &a, int i)
 {
-    // as in single-instance SSSP: stamping on nd < dv gives the same frontier
-    // as waiting for the atomic's old value
-    if (nd >= dv) return false;
-    atomic_min_dev_noret(&dist[v], nd);
-    stamp_base[v] = next;
-    return true;
+    const Inst &d = a.inst[i];
+    return Range{global_ptr(d.col), global_ptr(d.w), global_ptr(d.dist), global_ptr(a.mark + a.vbase[i]), 0, 0, 0u,
+                 d.m};
 }
 
-// kUnroll edges per lane: e_k = first + k * stride (< end) of one instance.
-__device__ __forceinline__ bool relax_batch(const Inst &d, int *stamp_base, int first, int stride, int end,
-                                            uint32_t du, int next)
+// K loaded edges a lane (v[k] < 0: none), nd[k] the distances they offer.  An edge
+// is dropped by the byte that bounds its target's distance (bound_code), which takes
+// half the cache and which no atomic touches; the others read the distance itself
+// (the drains of the later rounds 20 % faster, the first dense ones even).  The mark
+// that a relaxation leaves carries the bound of the distance it offers: the vertex's
+// own is never above any of them, whichever store comes last.  Marking on nd < the
+// distance read gives the same frontier as waiting for the atomic's old value, as in
+// single-instance SSSP.
+template <int K>
+__device__ __forceinline__ bool relax_loaded(const Range *const (&t)[K], int (&v)[K], const uint32_t (&nd)[K],
+                                             int next)
 {
-    int v[kUnroll];
-    uint32_t wt[kUnroll], dv[kUnroll];
-#pragma unroll
-    for (int k = 0; k < kUnroll; ++k) {
-        const int e = first + k * stride;
-        const bool ok = e < end;
-        v[k] = ok ? d.col[e] : -1;
-        wt[k] = ok ? d.w[e] : 0u;
-    }
-#pragma unroll
-    for (int k = 0; k < kUnroll; ++k) dv[k] = v[k] >= 0 ? d.dist[v[k]] : 0u;
+    uint32_t dv[K];
     bool any = false;
 #pragma unroll
-    for (int k = 0; k < kUnroll; ++k)
-        if (v[k] >= 0) any |= relax_loaded(d.dist, stamp_base, v[k], add_sat(du, wt[k]), dv[k], next);
+    for (int k = 0; k < K; ++k) dv[k] = v[k] >= 0 ? t[k]->mark[v[k]] & 255u : 0u;
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = nd[k] < bound_value(dv[k]) ? v[k] : -1;
+#pragma unroll
+    for (int k = 0; k < K; ++k) dv[k] = v[k] >= 0 ? t[k]->dist[v[k]] : 0u;
+#pragma unroll
+    for (int k = 0; k < K; ++k) {
+        if (v[k] < 0 || nd[k] >= dv[k]) continue;
+        (void)__hip_atomic_fetch_min(&t[k]->dist[v[k]], nd[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        t[k]->mark[v[k]] = (uint16_t)(next << 8 | bound_code(nd[k]));
+        any = true;
+    }
+    return any;
+}
+
+// four consecutive entries of a row, which starts anywhere
+typedef int Quad __attribute__((ext_vector_type(4), aligned(4)));
+
+// The four edges from e on, of a range with e < end in an instance of at least
+// four edges: one load an array, moved down where it would pass the end of the
+// array.  v is -1 where there is no edge.
+__device__ __forceinline__ void load_quad(const Range &t, int e, int *v, uint32_t *w)
+{
+    const int q = min(e, t.m - 4);
+    const Quad c = *(gptr<const Quad>)(t.col + q), x = *(gptr<const Quad>)(t.w + q);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        v[k] = q + k >= e && q + k < t.end ? c[k] : -1;
+        w[k] = (uint32_t)x[k];
+    }
+}
+
+// The edges [e, t.end) of a range by a group of lanes (e: the lane's first), U
+// times four consecutive edges a lane and step; a step of the group is U * stride
+// edges.
+template <int U>
+__device__ __forceinline__ bool relax_quads(const Range &t, int e, int stride, int next)
+{
+    bool any = false;
+    for (; e < t.end; e += U * stride) {
+        int v[4 * U];
+        uint32_t w[4 * U];
+        const Range *range[4 * U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (e + u * stride < t.end) {
+                load_quad(t, e + u * stride, v + 4 * u, w + 4 * u);
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) v[4 * u + k] = -1, w[4 * u + k] = 0u;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 4 * U; ++k) w[k] = add_sat(t.du, w[k]), range[k] = &t;
+        any |= relax_loaded<4 * U>(range, v, w, next);
+    }
+    return any;
+}
+
+// The same by one lane and edge by edge (an instance of fewer than four edges).
+__device__ __forceinline__ bool relax_single(const Range &t, int next)
+{
+    bool any = false;
+    for (int e = t.beg; e < t.end; ++e) {
+        const Range *range[1] = {&t};
+        int v[1] = {t.col[e]};
+        const uint32_t nd[1] = {add_sat(t.du, t.w[e])};
+        any |= relax_loaded<1>(range, v, nd, next);
+    }
     return any;
 }
 
@@ -114,7 +186,7 @@ __global__ void batch_init(BatchArgs a)
         const int v = g - a.vbase[i];
         const bool s = v == d.src;
         d.dist[v] = s ? 0u : kInf;
-        a.stamp[g] = s ? 0 : -1;
+        a.mark[g] = s ? 0 : 0xffff;
         a.relaxed_at[g] = kInf;
     }
     if (blockIdx.x == 0 && threadIdx.x < 3) {
@@ -123,22 +195,52 @@ __global__ void batch_init(BatchArgs a)
     }
 }
 
+// Windows of BLOCK vertices whose marks a block of batch_round reads together.
+constexpr int kWindowsPerStep = 4;
+
+// Lanes of a buffered item of up to kShortItem edges, and of a longer one.
+constexpr int kShortItem = 32, kShortLanes = 4, kLongLanes = 16;
+
 template <int BLOCK>
 struct BatchLds {
-    int inst[BLOCK];
-    int beg[BLOCK];
-    int end[BLOCK];
-    int csz[BLOCK];
-    uint32_t du[BLOCK];
-    int pre[BLOCK + 1];
+    int list[BLOCK * kWindowsPerStep];
+    Range item[BLOCK];
+    int count[3];
     int scan_tmp[2 * (BLOCK / kWave)];
     int base;
 };
 
-// Windows of BLOCK vertices whose frontier stamps a block of batch_round
-// reads together.
-constexpr int kWindowsPerStep = 8;
+// The consolidated child of a wave or a block over its buffer: ns short items
+// from item[0] up and nl long ones from item[cap - 1] down, by wave `wid` of nw.
+__device__ __forceinline__ bool relax_buffer(const Range *item, int cap, int ns, int nl, int wid, int nw, int next)
+{
+    constexpr int kLongTask = kWave / kLongLanes, kShortTask = kWave / kShortLanes;
+    const int short0 = (nl + kLongTask - 1) / kLongTask, tasks = short0 + (ns + kShortTask - 1) / kShortTask;
+    const int lane = lane_id();
+    bool any = false;
+    for (int t = wid; t < tasks; t += nw) {
+        const bool lng = t < short0;
+        const int lanes = lng ? kLongLanes : kShortLanes;
+        const int i = (lng ? t : t - short0) * (kWave / lanes) + lane / lanes;
+        if (i < (lng ? nl : ns)) {
+            const Range it = item[lng ? cap - 1 - i : i];
+            any |= relax_quads<1>(it, it.beg + 4 * (lane & (lanes - 1)), 4 * lanes, next);
+        }
+    }
+    return any;
+}
 
+// Round r over the vertices of all instances.  A block reads the marks of
+// kWindowsPerStep windows, lists the frontier vertices among them in LDS and takes
+// BLOCK of them at a time, so that a sparse round pays the chain of dependent loads
+// (instance, row range, edges, distances) once a step and not once a window.
+// Bound by that chain where the frontier is sparse, and by the relaxations' random
+// accesses where it is dense (62M edges relaxed in a batch of 64 power-law graphs of
+// 2^10 to 2^17 vertices, 16 edges each; its random reads run at about 140 G/s).
+// That batch, 16 rounds: block level 1,414 -> 880 us in this kernel and 2.04 ->
+// 1.44 ms a call (thread-strided single edges, a window at a time, generic
+// pointers before), wave level 2.83 -> 1.56 ms, grid level 1.76 -> 1.51 ms.  Eight
+// windows a step: 2 to 5 % slower (4 % faster in batches of 256); two: 5 % slower.
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) void batch_round(BatchArgs a, int r)
 {
@@ -151,194 +253,141 @@ __global__ __launch_bounds__(BLOCK) void batch_round(BatchArgs a, int r)
     }
     if (!act) return;
     const int next = r + 1;
-    const int lane = lane_id();
+    const int tid = threadIdx.x, lane = lane_id(), wid = tid / kWave;
     StatAcc acc;
-    // the stamps of S windows are read together and a block skips all S at
-    // once when none of them holds a frontier vertex
+    bool any = false;
     constexpr int S = kWindowsPerStep;
     const int stride = gridDim.x * BLOCK;
+    if (tid < 3) sb.count[tid] = 0;
+    __syncthreads();
+    int step = 0;
     for (long long wbase = (long long)blockIdx.x * BLOCK; wbase < a.total; wbase += (long long)S * stride) {
-        int bits = 0;
+        int mark[S];
 #pragma unroll
         for (int w = 0; w < S; ++w) {
-            const long long gg = wbase + (long long)w * stride + threadIdx.x;
-            if (gg < a.total && a.stamp[gg] == r) bits |= 1 << w;
+            const long long gg = wbase + (long long)w * stride + tid;
+            mark[w] = gg < a.total ? a.mark[gg] >> 8 : -1;
         }
-        if (!__syncthreads_or(bits)) continue;
+        uint64_t mask[S];
+        int mine = 0;
+#pragma unroll
         for (int w = 0; w < S; ++w) {
-            const long long base_l = wbase + (long long)w * stride;
-            if (base_l >= a.total) break;  // uniform in the block
-            const int base = (int)base_l;
-            const int g = base + threadIdx.x;
-            const bool member = (bits >> w) & 1;
-            int i = 0, beg = 0, end = 0, mode = WC_FLAT;
-            uint32_t du = 0;
+            mask[w] = __ballot(mark[w] == (r & 255));
+            mine += __builtin_popcountll(mask[w]);
+        }
+        if (mine) {
+            int at = 0;
+            if (lane == 0) at = atomicAdd(&sb.count[step], mine);
+            at = readlane(at, 0);
+#pragma unroll
+            for (int w = 0; w < S; ++w) {
+                if (mark[w] == (r & 255)) sb.list[at + rank_in(mask[w])] = (int)(wbase + (long long)w * stride) + tid;
+                at += __builtin_popcountll(mask[w]);
+            }
+        }
+        // the counter after the next one was last read two barriers ago
+        const int after = step == 2 ? 0 : step + 1;
+        if (tid == 0) sb.count[after] = 0;
+        __syncthreads();
+        const int members = sb.count[step];
+        step = after;
+        for (int m0 = 0; m0 < members; m0 += BLOCK) {
+            const bool member = m0 + tid < members;
+            int g = 0, mode = WC_FLAT, chunk = 1, deg = 0;
+            Range t = {};
             if (member) {
-                i = find_inst(a, g);
+                g = sb.list[m0 + tid];
+                const int i = find_inst(a, g);
                 const Inst &d = a.inst[i];
                 const int v = g - a.vbase[i];
-                beg = d.row_ptr[v];
-                end = d.row_ptr[v + 1];
-                du = d.dist[v];
+                t = make_range(a, i);
+                const gptr<const int> row = global_ptr(d.row_ptr);
+                t.beg = row[v];
+                t.end = row[v + 1];
+                t.du = t.dist[v];
+                chunk = d.chunk;
                 // already relaxed with its present distance (it improved before its
                 // own relaxations read it): nothing to do
-                if (a.relaxed_at[g] == du) end = beg;
-                mode = end - beg > d.threshold ? d.mode : WC_FLAT;
+                if (a.relaxed_at[g] == t.du) t.end = t.beg;
+                deg = t.end - t.beg;
+                mode = deg > d.threshold ? d.mode : WC_FLAT;
                 // a wave's or block's own child keeps items of up to one chunk;
                 // longer ones go to the grid-wide drain (the KC_X rule of
                 // Sec. IV.E: a warp's or block's child gets many blocks)
-                if ((mode == WC_WAVE || mode == WC_BLOCK) && end - beg > d.chunk) mode = WC_GRID;
+                if ((mode == WC_WAVE || mode == WC_BLOCK) && deg > chunk) mode = WC_GRID;
                 // wave, block and inline work use this reading; grid chunks raise
                 // the value from 0 in the drain (or it stays du on overflow)
-                if (end > beg && mode != WC_GRID) a.relaxed_at[g] = du;
+                if (deg > 0 && mode != WC_GRID) a.relaxed_at[g] = t.du;
             }
-            const int deg = end - beg;
-            const bool heavy = mode != WC_FLAT;
             if (a.want_stats) {
                 acc.edges += deg;
-                acc.buffered += heavy ? deg : 0;
-                acc.items += heavy ? 1 : 0;
+                acc.buffered += mode != WC_FLAT ? deg : 0;
+                acc.items += mode != WC_FLAT ? 1 : 0;
             }
-            bool any = false;
-            if (member && !heavy) any = [&] {
-                const Inst &d = a.inst[i];
-                int *sbase = a.stamp + a.vbase[i];
-                bool f = false;
-                for (int e = beg; e < end; e += kUnroll) f |= relax_batch(d, sbase, e, 1, end, du, next);
-                return f;
-            }();
-            // wave-level items: the ballot mask is the buffer, the wave drains it
-            uint64_t wmask = a.has_wave ? __ballot(mode == WC_WAVE) : 0ull;
-            if (a.want_stats && wmask && lane == 0) acc.dispatches += 1;
-            while (wmask) {
-                const int b = __builtin_ctzll(wmask);
-                wmask &= wmask - 1;
-                const int ii = readlane(i, b);
-                const Inst &d = a.inst[ii];
-                int *sbase = a.stamp + a.vbase[ii];
-                const int ub = readlane(beg, b), ue = readlane(end, b);
-                const uint32_t ud = readlane_u(du, b);
-                for (int e0 = ub; e0 < ue; e0 += kWave * kUnroll)
-                    any |= relax_batch(d, sbase, e0 + lane, kWave, ue, ud, next);
+            // inline work: light vertices, 8 edges at a time
+            if (mode == WC_FLAT && deg > 0) any |= t.m >= 4 ? relax_quads<1>(t, t.beg, 4, next) : relax_single(t, next);
+            const bool lng = deg > kShortItem;
+            // wave-level items: a part of the buffer of the wave's own, no barrier
+            if (a.has_wave) {
+                const bool it = mode == WC_WAVE;
+                const uint64_t shorts = __ballot(it && !lng), longs = __ballot(it && lng);
+                if (shorts | longs) {
+                    if (a.want_stats && lane == 0) acc.dispatches += 1;
+                    Range *const buf = sb.item + wid * kWave;
+                    if (it) buf[lng ? kWave - 1 - rank_in(longs) : rank_in(shorts)] = t;
+                    wave_lds_sync();
+                    any |= relax_buffer(buf, kWave, __builtin_popcountll(shorts), __builtin_popcountll(longs), 0, 1,
+                                        next);
+                    wave_lds_sync();
+                }
             }
-            // block-level items: LDS buffer, barrier, flattened drain by the block
-            if (a.has_block) {
-                const bool bl = mode == WC_BLOCK;
-                int k, off, nb, total;
-                block_scan2<BLOCK>(bl ? 1 : 0, bl ? deg : 0, sb.scan_tmp, k, off, nb, total);
-                if (bl) {
-                    sb.inst[k] = i;
-                    sb.beg[k] = beg;
-                    sb.du[k] = du;
-                    sb.pre[k] = off;
-                }
-                if (threadIdx.x == 0) {
-                    sb.pre[nb] = total;
-                    if (a.want_stats && nb) acc.dispatches += 1;
-                }
-                __syncthreads();
-                int it = 0;
-                for (int j = threadIdx.x; j < total; j += BLOCK) {
-                    while (it + 1 < nb && sb.pre[it + 1] <= j) ++it;
-                    const Inst &d = a.inst[sb.inst[it]];
-                    const int e = sb.beg[it] + (j - sb.pre[it]);
-                    const int v = d.col[e];
-                    const uint32_t nd = add_sat(sb.du[it], d.w[e]);
-                    any |= relax_loaded(d.dist, a.stamp + a.vbase[sb.inst[it]], v, nd, d.dist[v], next);
-                }
-                __syncthreads();
+            if (!a.has_block && !a.has_grid) continue;
+            // block-level items go to the buffer in LDS, grid-level ones as chunks to
+            // the global buffer, reserved with one atomic a block
+            const bool bl = mode == WC_BLOCK;
+            const int nch = mode == WC_GRID ? (deg + chunk - 1) / chunk : 0;
+            int at, off, nb, tot;
+            block_scan2<BLOCK>(bl ? (lng ? 1 << 16 : 1) : 0, nch, sb.scan_tmp, at, off, nb, tot);
+            if (bl) sb.item[lng ? BLOCK - 1 - (at >> 16) : at & 0xffff] = t;
+            if (tid == 0) {
+                if (tot) sb.base = atomic_add_dev(&a.chunk_tail[(r % 3) * kPad], tot);
+                if (a.want_stats && nb) acc.dispatches += 1;
             }
-            // grid-level items: chunks into the global buffer (block-aggregated reservation)
-            if (a.has_grid) {
-                const bool gr = mode == WC_GRID;
-                int chunk = 1, nch = 0;
-                if (gr) {
-                    chunk = a.inst[i].chunk;
-                    nch = (deg + chunk - 1) / chunk;
-                }
-                int excl, d0, tot, d1;
-                block_scan2<BLOCK>(nch, 0, sb.scan_tmp, excl, d0, tot, d1);
-                sb.pre[threadIdx.x] = excl;
-                sb.inst[threadIdx.x] = i;
-                sb.beg[threadIdx.x] = beg;
-                sb.end[threadIdx.x] = end;
-                sb.csz[threadIdx.x] = chunk;
-                sb.du[threadIdx.x] = du;
-                if (threadIdx.x == 0) sb.base = tot ? atomic_add_dev(&a.chunk_tail[(r % 3) * kPad], tot) : 0;
-                __syncthreads();
-                const int slot0 = sb.base;
-                if (nch > 0) a.relaxed_at[g] = (long long)slot0 + excl + nch > a.chunk_cap ? du : 0u;
-                // the block writes the window's chunks together: chunk j belongs to
-                // the last thread whose offset is <= j
-                for (int j = threadIdx.x; j < tot; j += BLOCK) {
-                    int lo = 0, hi = BLOCK - 1;
-                    while (lo < hi) {
-                        const int mid = (lo + hi + 1) >> 1;
-                        if (sb.pre[mid] <= j) lo = mid;
-                        else hi = mid - 1;
-                    }
-                    const int ck = sb.csz[lo];
-                    const int cb = sb.beg[lo] + (j - sb.pre[lo]) * ck, ce = min(sb.end[lo], cb + ck);
-                    const int oi = sb.inst[lo];
-                    if ((long long)slot0 + j < a.chunk_cap) {
-                        a.chunks[slot0 + j] = make_int4(base + lo, cb, ce, oi);
+            __syncthreads();
+            if (nb) any |= relax_buffer(sb.item, BLOCK, nb & 0xffff, nb >> 16, wid, BLOCK / kWave, next);
+            if (tot) {
+                const long long slot = (long long)sb.base + off;
+                if (nch > 0) a.relaxed_at[g] = slot + nch > a.chunk_cap ? t.du : 0u;
+                for (int c = 0; c < nch; ++c) {
+                    const int cb = t.beg + c * chunk, ce = min(t.end, cb + chunk);
+                    if (slot + c < a.chunk_cap) {
+                        a.chunks[slot + c] = make_int4(g, cb, ce, find_inst(a, g));
                     } else {
                         a.stats->overflowed = 1;
-                        const Inst &d = a.inst[oi];
-                        int *sbase = a.stamp + a.vbase[oi];
-                        for (int e = cb; e < ce; e += kUnroll) any |= relax_batch(d, sbase, e, 1, ce, sb.du[lo], next);
+                        Range part = t;
+                        part.beg = cb;
+                        part.end = ce;
+                        any |= relax_single(part, next);
                     }
                 }
-                __syncthreads();
             }
-            if (__ballot(any) && lane == 0) a.active[((r + 1) % 3) * kPad] = 1;
+            __syncthreads();  // the buffers' readers, before the next members
         }
+        if (members) __syncthreads();  // the list's readers, before the next step
     }
+    if (__ballot(any) && lane == 0) a.active[((r + 1) % 3) * kPad] = 1;
     if (a.want_stats) stat_flush(a.stats, acc);
 }
 
-// Two chunks at once (uniform arguments; the chunks may belong to different
-// instances): each lane keeps 2 * kUnroll edges in flight.  The source
-// distances are read after the edges are requested; the distances used are
-// returned.  Chunk 1 may be empty (cb1 == ce1).
-__device__ __forceinline__ bool relax_pair(const BatchArgs &a, int g0, int i0, int cb0, int ce0, int g1, int i1,
-                                           int cb1, int ce1, int next, uint32_t &du0_used, uint32_t &du1_used)
-{
-    const Inst &d0 = a.inst[i0];
-    const Inst &d1 = a.inst[i1];
-    const int vb0 = a.vbase[i0], vb1 = a.vbase[i1];
-    int *sb0 = a.stamp + vb0;
-    int *sb1 = a.stamp + vb1;
-    bool any = false;
-    du0_used = du1_used = 0u;
-    const int len = max(ce0 - cb0, ce1 - cb1);
-    for (int o = lane_id(); o - lane_id() < len; o += kWave * kUnroll) {
-        int v[2 * kUnroll];
-        uint32_t wt[2 * kUnroll], dv[2 * kUnroll];
-#pragma unroll
-        for (int k = 0; k < 2 * kUnroll; ++k) {
-            const bool first = k < kUnroll;
-            const int e = (first ? cb0 : cb1) + o + (k % kUnroll) * kWave;
-            const bool ok = e < (first ? ce0 : ce1);
-            v[k] = ok ? (first ? d0.col[e] : d1.col[e]) : -1;
-            wt[k] = ok ? (first ? d0.w[e] : d1.w[e]) : 0u;
-        }
-        const uint32_t du0 = d0.dist[g0 - vb0];
-        const uint32_t du1 = cb1 < ce1 ? d1.dist[g1 - vb1] : 0u;
-        du0_used = max(du0_used, du0);
-        du1_used = max(du1_used, du1);
-#pragma unroll
-        for (int k = 0; k < 2 * kUnroll; ++k) dv[k] = v[k] >= 0 ? (k < kUnroll ? d0.dist[v[k]] : d1.dist[v[k]]) : 0u;
-#pragma unroll
-        for (int k = 0; k < 2 * kUnroll; ++k)
-            if (v[k] >= 0) {
-                const bool first = k < kUnroll;
-                any |= relax_loaded(first ? d0.dist : d1.dist, first ? sb0 : sb1, v[k],
-                                    add_sat(first ? du0 : du1, wt[k]), dv[k], next);
-            }
-    }
-    return any;
-}
+// The chunks of round r's global buffer: half a wave a chunk and two chunks of it
+// at a time (of any instances), four consecutive edges a lane and load, so that a
+// chunk of 128 edges is one load an array.  The source distances are read after
+// the edges are requested; the largest one used raises relaxed_at.  606 -> 490 us
+// in the batch of 64 (a wave a chunk, one edge a lane and load before).
+// The drain's grid, in resident grids: the hardware then hands out the chunks in
+// their order, so that those in flight are near each other (the batch of 64: 1.52,
+// 1.48, 1.44 ms a call at 1, 2, 4; 16 pays for empty blocks in the sparse rounds).
+constexpr int kDrainWaves = 4;
 
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) void batch_drain(BatchArgs a, int r)
@@ -351,24 +400,56 @@ __global__ __launch_bounds__(BLOCK) void batch_drain(BatchArgs a, int r)
     const int nw = gridDim.x * (BLOCK / kWave);
     if (a.want_stats && blockIdx.x == 0 && threadIdx.x == 0 && total > 0)
         atomic_add_dev(&a.stats->rep[0].dispatches, 1ull);
+    constexpr int kHalf = kWave / 2, kStep = 4 * kHalf;
+    const int half = lane_id() / kHalf, sub = lane_id() & (kHalf - 1);
     bool any = false;
-    // two chunks per wave and step; the next pair's entries are fetched before
-    // the current pair's edges
-    int4 q0 = load_or_zero(a.chunks, gw, gw < total);
-    int4 q1 = load_or_zero(a.chunks, gw + nw, gw + nw < total);
-    for (int c = gw; c < total; c += 2 * nw) {
-        const int g0 = __builtin_amdgcn_readfirstlane(q0.x), i0 = __builtin_amdgcn_readfirstlane(q0.w);
-        const int cb0 = __builtin_amdgcn_readfirstlane(q0.y), ce0 = __builtin_amdgcn_readfirstlane(q0.z);
-        const int g1 = __builtin_amdgcn_readfirstlane(q1.x), i1 = __builtin_amdgcn_readfirstlane(q1.w);
-        const int cb1 = __builtin_amdgcn_readfirstlane(q1.y), ce1 = __builtin_amdgcn_readfirstlane(q1.z);
-        const int cn = c + 2 * nw;
-        q0 = load_or_zero(a.chunks, cn, cn < total);
-        q1 = load_or_zero(a.chunks, cn + nw, cn + nw < total);
-        uint32_t du0, du1;
-        any |= relax_pair(a, g0, i0, cb0, ce0, g1, i1, cb1, ce1, next, du0, du1);
-        if (lane_id() == 0) {
-            atomic_max_dev_noret(&a.relaxed_at[g0], du0);
-            if (cb1 < ce1) atomic_max_dev_noret(&a.relaxed_at[g1], du1);
+    // the next entries are fetched before the current chunks' edges
+    const long long first = gw + (long long)half * nw, step = 4ll * nw;
+    int4 q[2];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) q[p] = load_or_zero(a.chunks, first + 2ll * p * nw, first + 2ll * p * nw < total);
+    for (long long c = first; c < total; c += step) {
+        Range t[2];
+        int src[2], gid[2];
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            gid[p] = q[p].x;
+            t[p] = make_range(a, q[p].w);
+            src[p] = gid[p] - a.vbase[q[p].w];
+            t[p].beg = q[p].y;
+            t[p].end = q[p].z;
+            const long long n = c + step + 2ll * p * nw;
+            q[p] = load_or_zero(a.chunks, n, n < total);
+        }
+        const int len = max(t[0].end - t[0].beg, t[1].end - t[1].beg);
+        uint32_t used[2] = {0u, 0u};
+        for (int o = 4 * sub; o - 4 * sub < len; o += kStep) {
+            int v[8];
+            uint32_t w[8];
+            const Range *range[8];
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                const int e = t[p].beg + o;
+                if (e < t[p].end) {
+                    load_quad(t[p], e, v + 4 * p, w + 4 * p);
+                } else {
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) v[4 * p + k] = -1, w[4 * p + k] = 0u;
+                }
+            }
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                t[p].du = t[p].beg < t[p].end ? t[p].dist[src[p]] : 0u;
+                used[p] = max(used[p], t[p].du);
+            }
+#pragma unroll
+            for (int k = 0; k < 8; ++k) w[k] = add_sat(t[k / 4].du, w[k]), range[k] = &t[k / 4];
+            any |= relax_loaded<8>(range, v, w, next);
+        }
+        if (sub == 0) {
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+                if (t[p].beg < t[p].end) atomic_max_dev_noret(&a.relaxed_at[gid[p]], used[p]);
         }
     }
     if (__ballot(any) && lane_id() == 0) a.active[((r + 1) % 3) * kPad] = 1;
@@ -447,7 +528,7 @@ extern "C" wc_status wc_sssp_batch(wc_ctx *ctx, int32_t count, const wc_csr *gra
         if (cfg.driver != 0) return fail(WC_EINVAL, "wc_sssp_batch: the persistent driver is disabled");
         const int chunk = kWave * cfg.items_per_lane;
         inst[i] = Inst{g.row_ptr, g.col, w[i], dist[i], g.n, (int)mode, mode == WC_FLAT ? 0x7fffffff : cfg.threshold,
-                       chunk, src[i], 0};
+                       chunk, src[i], (int)g.m};
         has[mode] = 1;
         vbase[i] = (int)total;
         total += g.n;
@@ -464,17 +545,19 @@ extern "C" wc_status wc_sssp_batch(wc_ctx *ctx, int32_t count, const wc_csr *gra
     BatchKernels ks = pick(block);
     const int resident = resident_blocks(ctx, ks.round, block);
     const int windows = (int)((total + block - 1) / block);
-    // With wave- or block-level instances the parent takes one step of
-    // kWindowsPerStep windows per workgroup, so the hardware hands the steps
-    // dense with buffered vertices to CUs as they free up (512 instances, all
-    // block / all wave: 15.8 -> 14.1 ms, 20.5 -> 16.9 ms); grid-level
-    // instances alone keep the resident grid (15.2 against 15.5 ms).
-    const int grid = std::max(1, has[WC_WAVE] || has[WC_BLOCK] ? (windows + kWindowsPerStep - 1) / kWindowsPerStep
-                                                              : std::min(resident, windows));
-    const int dgrid = std::max(1, resident);
+    // The resident grid, or a workgroup for each window of a small batch.  With
+    // wave- or block-level instances also at least a workgroup for each step of
+    // kWindowsPerStep windows, so the hardware hands the steps dense with buffered
+    // vertices to CUs as they free up (block level, 64 instances of 2^10 to 2^17
+    // vertices: 1.47 -> 1.43 ms; 16 of 2^8 to 2^12, of 85 windows: 0.46 ms by steps
+    // alone, 0.32 ms by windows); grid-level instances keep the resident grid
+    // (64: 1.51 against 1.50 ms, 16: 0.26 against 0.31 ms).
+    int grid = std::max(1, std::min(resident, windows));
+    if (has[WC_WAVE] || has[WC_BLOCK]) grid = std::max(grid, (windows + kWindowsPerStep - 1) / kWindowsPerStep);
+    const int dgrid = std::max(1, resident * kDrainWaves);
     const long long nwin = total / kWinInst + 1;
     const size_t blob = padded(sizeof(Inst) * count) + padded(4 * (count + 1)) + padded(4 * nwin);
-    size_t need = blob + 2 * padded(total * 4) + 2 * padded(3 * kPad * 4) + padded(cap * 16);
+    size_t need = blob + padded(total * 2) + padded(total * 4) + 2 * padded(3 * kPad * 4) + padded(cap * 16);
     wc_status st = pool_reserve(ctx, need, stream);
     if (st != WC_OK) return st;
     BatchArgs a;
@@ -485,7 +568,7 @@ extern "C" wc_status wc_sssp_batch(wc_ctx *ctx, int32_t count, const wc_csr *gra
     a.win_inst = reinterpret_cast<const int *>(d_blob + padded(sizeof(Inst) * count) + padded(4 * (count + 1)));
     a.count = count;
     a.total = (int)total;
-    a.stamp = pool_take<int>(ctx, total);
+    a.mark = pool_take<uint16_t>(ctx, total);
     a.relaxed_at = pool_take<uint32_t>(ctx, total);
     a.active = pool_take<int>(ctx, 3 * kPad);
     a.chunk_tail = pool_take<int>(ctx, 3 * kPad);

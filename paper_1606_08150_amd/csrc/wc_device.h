@@ -41,6 +41,23 @@ __device__ __forceinline__ gptr<T> global_ptr(T *p)
     return (gptr<T>)p;
 }
 
+// ---- upper bounds in a byte ---------------------------------------------------------------------
+// The smallest code whose value is at least d: exact up to 15, then 8 values an
+// octave (at most 1/8 above d); 255 for what passes the last octave.
+__device__ __forceinline__ uint8_t bound_code(uint32_t d)
+{
+    if (d < 8u) return static_cast<uint8_t>(d);
+    const int sh = 28 - __builtin_clz(d);
+    const uint32_t q = (d >> sh) + ((d & ((1u << sh) - 1u)) ? 1u : 0u);  // 8 .. 16
+    const uint32_t c = (static_cast<uint32_t>(sh) << 3) + q;             // 16: the next octave's first
+    return static_cast<uint8_t>(c > 239u ? 255u : c);
+}
+
+__device__ __forceinline__ uint32_t bound_value(uint32_t c)
+{
+    return c < 16u ? c : c > 239u ? 0xffffffffu : (8u | (c & 7u)) << ((c >> 3) - 1u);
+}
+
 // ---- guarded loads ---------------------------------------------------------------------------
 // arr[i] when ok, else zero, without a select between a global address and a
 // local temporary (which the compiler would otherwise materialise on the stack).
