@@ -40,6 +40,7 @@ namespace {
 
 constexpr int kPad = 32;  // ring entries live on separate 128-byte lines
 constexpr int kUnroll = 4;  // edges in flight per lane
+constexpr int kDrainUnroll = 2;  // ... and chunk in the drain: chunks hold 128 edges by default
 
 struct SsspArgs {
     const int *row_ptr;
@@ -49,11 +50,13 @@ struct SsspArgs {
     int *stamp;       // stamp[v] == r: v is a frontier vertex of round r
     uint32_t *relaxed_at;  // grid mode: the largest distance v's edges were last relaxed with;
                            // v is in the frontier while dist[v] is below it
+    uint8_t *bound;        // grid mode: bound_code of a distance that v had
     int *active;      // ring of 3 flags (stride kPad): round r has a frontier
     int *chunk_tail;  // ring of 3 grid-buffer tails (stride kPad)
     int4 *chunks;     // grid consolidation buffer: (u, begin, end, 0)
     long long chunk_cap;
     int n;
+    int m;
     int threshold;
     int chunk;
     int spill;        // wave and block modes: buffered items with more edges go to the global buffer
@@ -87,7 +90,67 @@ __device__ __forceinline__ bool relax_loaded(const SsspArgs &a, int v, uint32_t 
     if (nd >= dv) return false;
     atomic_min_dev_noret(&a.dist[v], nd);
     if (STAMP) a.stamp[v] = next;
+    else a.bound[v] = bound_code(nd);
     return true;
+}
+
+// four consecutive entries of a row, which starts anywhere
+typedef int Quad __attribute__((ext_vector_type(4), aligned(4)));
+
+// The four edges from e on (e < end): one load an array, moved down where it would
+// pass the end of the array.  v is -1 where there is no edge.
+__device__ __forceinline__ void load_quad(const SsspArgs &a, int e, int end, int *v, uint32_t *w)
+{
+    if (a.m >= 4) {
+        const int q = min(e, a.m - 4);
+        const Quad c = *reinterpret_cast<const Quad *>(a.col + q);
+        Quad x = {1, 1, 1, 1};
+        if (a.w) x = *reinterpret_cast<const Quad *>(a.w + q);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            v[k] = q + k >= e && q + k < end ? c[k] : -1;
+            w[k] = static_cast<uint32_t>(x[k]);
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            v[k] = e + k < end ? a.col[e + k] : -1;
+            w[k] = e + k < end ? weight(a, e + k) : 0u;
+        }
+    }
+}
+
+// K loaded edges a lane (v[k] < 0: none), nd[k] the distances they offer.  In grid
+// mode an edge is dropped by the byte that bounds its target's distance, which takes
+// a quarter of the cache and which no atomic touches; the others go to the atomic
+// without a look at the distance, and leave the bound of what they offer: the
+// vertex's own distance is never above that of any of them, whichever store comes
+// last.  (A relaxation that only the bound let through lowers nothing; at worst it
+// makes the call look once more for a frontier.  Counted runs read the distance.)
+// 150,001 vertices, 2.4M edges: 303 us a call by reading every distance, 254 by
+// reading those that pass the bound, 237 by reading none; 2^22 vertices, 67M edges:
+// 2.07, 2.04 and 1.97 ms; levels of 2^20 vertices: 310, 301 and 284 us.
+template <bool STAMP, int K>
+__device__ __forceinline__ int relax_edges(const SsspArgs &a, int (&v)[K], const uint32_t (&nd)[K], int next)
+{
+    uint32_t dv[K];
+    if (!STAMP) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) dv[k] = v[k] >= 0 ? a.bound[v[k]] : 0u;
+#pragma unroll
+        for (int k = 0; k < K; ++k) v[k] = nd[k] < bound_value(dv[k]) ? v[k] : -1;
+    }
+#pragma unroll
+    for (int k = 0; k < K; ++k) dv[k] = kInf;
+    if (STAMP || a.want_stats) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) dv[k] = v[k] >= 0 ? a.dist[v[k]] : 0u;
+    }
+    int upd = 0;
+#pragma unroll
+    for (int k = 0; k < K; ++k)
+        if (v[k] >= 0) upd += relax_loaded<STAMP>(a, v[k], nd[k], dv[k], next);
+    return upd;
 }
 
 // U edges per lane at once: e_k = first + k * stride (valid while < end).
@@ -125,7 +188,7 @@ __device__ __forceinline__ int relax_lane(const SsspArgs &a, int beg, int end, u
 }
 
 // Two chunks of the grid buffer at once (uniform arguments): each lane keeps
-// 2 * kUnroll edges in flight.  The chunks' source distances are read after
+// 2 * kDrainUnroll edges in flight.  The chunks' source distances are read after
 // their edges are requested (they may have improved since the vertex was
 // buffered); the largest distance used per chunk is returned.  Chunk 1 may be
 // empty (cb1 == ce1, u1 unused).
@@ -137,25 +200,23 @@ __device__ __forceinline__ int relax_wave2(const SsspArgs &a, int u0, int cb0, i
     const int len = max(ce0 - cb0, ce1 - cb1);
     du0_used = 0u;
     du1_used = 0u;
-    for (int o = lane_id(); o - lane_id() < len; o += kWave * kUnroll) {
-        int v[2 * kUnroll];
-        uint32_t wt[2 * kUnroll], dv[2 * kUnroll];
+    for (int o = lane_id(); o - lane_id() < len; o += kWave * kDrainUnroll) {
+        int v[2 * kDrainUnroll];
+        uint32_t nd[2 * kDrainUnroll];
 #pragma unroll
-        for (int k = 0; k < 2 * kUnroll; ++k) {
-            const int e = (k < kUnroll ? cb0 : cb1) + o + (k % kUnroll) * kWave;
-            const bool ok = e < (k < kUnroll ? ce0 : ce1);
+        for (int k = 0; k < 2 * kDrainUnroll; ++k) {
+            const int e = (k < kDrainUnroll ? cb0 : cb1) + o + (k % kDrainUnroll) * kWave;
+            const bool ok = e < (k < kDrainUnroll ? ce0 : ce1);
             v[k] = ok ? a.col[e] : -1;
-            wt[k] = ok ? weight(a, e) : 0u;
+            nd[k] = ok ? weight(a, e) : 0u;
         }
         const uint32_t du0 = a.dist[u0];
         const uint32_t du1 = cb1 < ce1 ? a.dist[u1] : 0u;
         du0_used = max(du0_used, du0);
         du1_used = max(du1_used, du1);
 #pragma unroll
-        for (int k = 0; k < 2 * kUnroll; ++k) dv[k] = v[k] >= 0 ? a.dist[v[k]] : 0u;
-#pragma unroll
-        for (int k = 0; k < 2 * kUnroll; ++k)
-            if (v[k] >= 0) upd += relax_loaded<STAMP>(a, v[k], add_sat(k < kUnroll ? du0 : du1, wt[k]), dv[k], next);
+        for (int k = 0; k < 2 * kDrainUnroll; ++k) nd[k] = add_sat(k < kDrainUnroll ? du0 : du1, nd[k]);
+        upd += relax_edges<STAMP, 2 * kDrainUnroll>(a, v, nd, next);
     }
     return upd;
 }
@@ -443,29 +504,29 @@ __global__ __launch_bounds__(BLOCK) void sssp_round(SsspArgs a, int r)
     if (a.want_stats) stat_flush(a.stats, acc);
 }
 
-// Two light vertices' inline work at once: each lane keeps kUnroll edges of
-// each vertex in flight.
+// Two light vertices' inline work at once: each lane keeps four edges of each
+// vertex in flight.
 __device__ __forceinline__ int relax_lane2(const SsspArgs &a, int b0, int e0, uint32_t du0, int b1, int e1,
                                             uint32_t du1, int next)
 {
-    constexpr int U = kUnroll;
     int upd = 0;
     const int len = max(e0 - b0, e1 - b1);
-    for (int o = 0; o < len; o += U) {
-        int v[2 * U];
-        uint32_t nd[2 * U], dv[2 * U];
+    for (int o = 0; o < len; o += 4) {
+        int v[8];
+        uint32_t nd[8];
 #pragma unroll
-        for (int k = 0; k < 2 * U; ++k) {
-            const int e = (k < U ? b0 : b1) + o + (k % U);
-            const bool ok = e < (k < U ? e0 : e1);
-            v[k] = ok ? a.col[e] : -1;
-            nd[k] = ok ? add_sat(k < U ? du0 : du1, weight(a, e)) : 0u;
+        for (int p = 0; p < 2; ++p) {
+            const int e = (p ? b1 : b0) + o, end = p ? e1 : e0;
+            if (e < end) {
+                load_quad(a, e, end, v + 4 * p, nd + 4 * p);
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) v[4 * p + k] = -1, nd[4 * p + k] = 0u;
+            }
         }
 #pragma unroll
-        for (int k = 0; k < 2 * U; ++k) dv[k] = v[k] >= 0 ? a.dist[v[k]] : 0u;
-#pragma unroll
-        for (int k = 0; k < 2 * U; ++k)
-            if (v[k] >= 0) upd += relax_loaded<false>(a, v[k], nd[k], dv[k], next);
+        for (int k = 0; k < 8; ++k) nd[k] = add_sat(k < 4 ? du0 : du1, nd[k]);
+        upd += relax_edges<false, 8>(a, v, nd, next);
     }
     return upd;
 }
@@ -531,6 +592,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8))) void
                     beg[k] = a.row_ptr[u[k]];
                     end[k] = a.row_ptr[u[k] + 1];
                     du[k] = a.dist[u[k]];  // read again: it may have improved since the test
+                    a.bound[u[k]] = bound_code(du[k]);
                 }
             }
 #pragma unroll
@@ -550,7 +612,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8))) void
             if (STATS) acc.updates += upd_inline;
 #pragma unroll
             for (int k = 0; k < V; ++k)
-                if (end[k] > beg[k] && !heavy[k]) a.relaxed_at[u[k]] = du[k];
+                if (member[k] && !heavy[k]) a.relaxed_at[u[k]] = du[k];
             // most windows of a small frontier hold no heavy vertex: skip the scan
             if (!__syncthreads_or((heavy[0] || heavy[1]) ? 1 : 0)) {
                 mark_active(a, r, upd_inline > 0);
@@ -609,11 +671,15 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8))) void
     if (STATS) stat_flush(a.stats, acc);
 }
 
-// Consolidated child of grid-level consolidation: one wave per chunk, chunks
-// fetched grid-stride until the buffer is exhausted (moldable).  With STAMP
-// (wave and block modes) it drains the items their groups handed on, and
-// stamps improved vertices into the next frontier instead of keeping
-// relaxed_at.
+// Consolidated child of grid-level consolidation: one wave per chunk, two chunks
+// at a time, fetched grid-stride until the buffer is exhausted (moldable).  With
+// STAMP (wave and block modes) it drains the items their groups handed on, and
+// stamps improved vertices into the next frontier instead of keeping relaxed_at.
+// Adjacent lanes take adjacent edges: the columns of a row are sorted, so their
+// targets share lines (half a wave a chunk with four edges a lane and load: 10 to
+// 15 % slower).  Bound by the requests that a CU's cache can have under way, at
+// about 70 G edges/s in the dense rounds (the cache waits for data all but 1 % of
+// the time there), and by the 27 G/s of the atomics, a third of those rounds.
 template <int BLOCK, bool STAMP>
 __global__ __launch_bounds__(BLOCK) void sssp_drain(SsspArgs a, int r)
 {
@@ -681,34 +747,29 @@ constexpr int kSmallLight = 32;
 constexpr int kSmallMidLanes = 16;   // ... of up to kSmallMid edges; beyond, a wave
 constexpr int kSmallMid = 256;
 
-struct Quad {
-    int x[4];  // aligned to 4 bytes: a row starts anywhere
-};
-
 // The edges [e, end) of a vertex at distance du by a group of lanes: four
 // consecutive edges a lane and step (e: the lane's first), so that a row costs a
-// quarter of the loads. A quad never passes the end of the array (m >= 4).
-__device__ __forceinline__ void relax_small(const SsspArgs &a, int m, int e, int end, int stride, uint32_t du,
+// quarter of the loads.
+__device__ __forceinline__ void relax_small(const SsspArgs &a, int e, int end, int stride, uint32_t du,
                                             uint32_t *dist)
 {
     while (__any(e < end)) {
         if (e < end) {
-            const int q = min(e, m - 4);
-            const Quad v = *reinterpret_cast<const Quad *>(a.col + q);
-            Quad w = {{1, 1, 1, 1}};
-            if (a.w) w = *reinterpret_cast<const Quad *>(a.w + q);
+            int v[4];
+            uint32_t w[4];
+            load_quad(a, e, end, v, w);
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                if (q + k < e || q + k >= end) continue;
-                const uint32_t nd = add_sat(du, static_cast<uint32_t>(w.x[k]));
-                if (nd < dist[v.x[k]]) atomicMin(&dist[v.x[k]], nd);
+                if (v[k] < 0) continue;
+                const uint32_t nd = add_sat(du, w[k]);
+                if (nd < dist[v[k]]) atomicMin(&dist[v[k]], nd);
             }
         }
         e += 4 * stride;
     }
 }
 
-__global__ __launch_bounds__(kSmallBlock) void sssp_small(SsspArgs a, int m, int src)
+__global__ __launch_bounds__(kSmallBlock) void sssp_small(SsspArgs a, int src)
 {
     __shared__ uint32_t s_dist[kSmallN], s_at[kSmallN];
     __shared__ int s_ptr[kSmallN + 1], s_list[kSmallN], s_long[kSmallM / kSmallMid], s_count[2][3];
@@ -774,7 +835,7 @@ __global__ __launch_bounds__(kSmallBlock) void sssp_small(SsspArgs a, int m, int
                 if (i < light) u = s_list[i];
             }
             const int sub = lane & (g - 1);
-            relax_small(a, m, u >= 0 ? s_ptr[u] + 4 * sub : 0, u >= 0 ? s_ptr[u + 1] : 0, g, u >= 0 ? s_at[u] : 0u, s_dist);
+            relax_small(a, u >= 0 ? s_ptr[u] + 4 * sub : 0, u >= 0 ? s_ptr[u + 1] : 0, g, u >= 0 ? s_at[u] : 0u, s_dist);
         }
         __syncthreads();
     }
@@ -804,6 +865,7 @@ __global__ void sssp_init(SsspArgs a, int src)
         a.dist[i] = i == src ? 0u : kInf;
         if (a.stamp) a.stamp[i] = i == src ? 0 : -1;
         if (a.relaxed_at) a.relaxed_at[i] = kInf;
+        if (a.bound) a.bound[i] = i == src ? 0 : 255;
     }
     if (blockIdx.x == 0 && threadIdx.x < 3) {
         a.active[threadIdx.x * kPad] = threadIdx.x == 0 ? 1 : 0;
@@ -896,6 +958,7 @@ wc_status run_sssp(wc_ctx *ctx, const wc_csr *g, const uint32_t *w, int32_t src,
     const int grid_cap = std::max(1, std::min(cfg.grid, resident));
     const long long slices = cfg.buffer_alloc == 1 ? (long long)grid_cap * (cfg.block + 1) : 0;
     size_t need = padded(n * 4) + 2 * padded(3 * kPad * 4) + padded(cap * 16) + padded(slices * 16);
+    if (mode == WC_GRID) need += padded(n);
     st = pool_reserve(ctx, need, stream);
     if (st != WC_OK) return st;
     SsspArgs a;
@@ -906,6 +969,7 @@ wc_status run_sssp(wc_ctx *ctx, const wc_csr *g, const uint32_t *w, int32_t src,
     // the frontier: round stamps (flat, wave, block) or relaxed_at (grid)
     a.stamp = mode == WC_GRID ? nullptr : pool_take<int>(ctx, n);
     a.relaxed_at = mode == WC_GRID ? pool_take<uint32_t>(ctx, n) : nullptr;
+    a.bound = mode == WC_GRID ? pool_take<uint8_t>(ctx, n) : nullptr;
     a.active = pool_take<int>(ctx, 3 * kPad);
     a.chunk_tail = pool_take<int>(ctx, 3 * kPad);
     a.chunks = pool_take<int4>(ctx, cap);
@@ -913,6 +977,7 @@ wc_status run_sssp(wc_ctx *ctx, const wc_csr *g, const uint32_t *w, int32_t src,
     a.buffer_alloc = cfg.buffer_alloc;
     a.group_bufs = slices ? pool_take<int4>(ctx, slices) : nullptr;
     a.n = (int)n;
+    a.m = (int)m;
     a.threshold = cfg.threshold;
     a.chunk = chunk;
     // a group's own child keeps items of up to one chunk (measured at scale 22:
@@ -936,14 +1001,15 @@ wc_status run_sssp(wc_ctx *ctx, const wc_csr *g, const uint32_t *w, int32_t src,
     int grid = std::max(1, std::min(std::min(cfg.grid, resident), windows));
     if ((mode == WC_WAVE || mode == WC_BLOCK) && cfg.buffer_alloc == 0)
         grid = std::max(1, own_grid ? std::min(cfg.grid, windows) : windows);
-    const int dgrid = std::max(1, std::min(cfg.grid, resident));
+    // twice the resident grid where the caller has not sized it: the hardware hands
+    // out the chunks more nearly in their order (2^22 vertices: 1.59 -> 1.55 ms in the
+    // drains; four times: 2 % more there and the rounds of small graphs slower)
+    const int dgrid = std::max(1, std::min(cfg.grid, resident)) * (mode == WC_GRID && !own_grid ? 2 : 1);
     // a small graph in one launch, where the tune is the library's choice, nothing
-    // is counted and the stages need no times of their own (its loads take four
-    // edges, so there have to be four)
-    if (mode == WC_GRID && n <= kSmallN && m >= 4 && m <= kSmallM && cfg.driver == 0 && !stats && !ctx->timing &&
+    // is counted and the stages need no times of their own
+    if (mode == WC_GRID && n <= kSmallN && m <= kSmallM && cfg.driver == 0 && !stats && !ctx->timing &&
         !cfg.own_shape && !(tune && (tune->threshold > 0 || tune->buf_capacity > 0))) {
-        int edges = static_cast<int>(m);
-        void *args[] = {&a, &edges, &src};
+        void *args[] = {&a, &src};
         return launch(ctx, "sssp_small", reinterpret_cast<const void *>(&sssp_small), dim3(1), dim3(kSmallBlock), args,
                       stream);
     }
