@@ -749,19 +749,20 @@ constexpr int kSmallMid = 256;
 
 // The edges [e, end) of a vertex at distance du by a group of lanes: four
 // consecutive edges a lane and step (e: the lane's first), so that a row costs a
-// quarter of the loads.
+// quarter of the loads.  A quad never passes the end of the arrays (m >= 4).
 __device__ __forceinline__ void relax_small(const SsspArgs &a, int e, int end, int stride, uint32_t du,
                                             uint32_t *dist)
 {
     while (__any(e < end)) {
         if (e < end) {
-            int v[4];
-            uint32_t w[4];
-            load_quad(a, e, end, v, w);
+            const int q = min(e, a.m - 4);
+            const Quad v = *reinterpret_cast<const Quad *>(a.col + q);
+            Quad w = {1, 1, 1, 1};
+            if (a.w) w = *reinterpret_cast<const Quad *>(a.w + q);
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                if (v[k] < 0) continue;
-                const uint32_t nd = add_sat(du, w[k]);
+                if (q + k < e || q + k >= end) continue;
+                const uint32_t nd = add_sat(du, static_cast<uint32_t>(w[k]));
                 if (nd < dist[v[k]]) atomicMin(&dist[v[k]], nd);
             }
         }
@@ -1006,8 +1007,9 @@ wc_status run_sssp(wc_ctx *ctx, const wc_csr *g, const uint32_t *w, int32_t src,
     // drains; four times: 2 % more there and the rounds of small graphs slower)
     const int dgrid = std::max(1, std::min(cfg.grid, resident)) * (mode == WC_GRID && !own_grid ? 2 : 1);
     // a small graph in one launch, where the tune is the library's choice, nothing
-    // is counted and the stages need no times of their own
-    if (mode == WC_GRID && n <= kSmallN && m <= kSmallM && cfg.driver == 0 && !stats && !ctx->timing &&
+    // is counted and the stages need no times of their own (its loads take four
+    // edges, so there have to be four)
+    if (mode == WC_GRID && n <= kSmallN && m >= 4 && m <= kSmallM && cfg.driver == 0 && !stats && !ctx->timing &&
         !cfg.own_shape && !(tune && (tune->threshold > 0 || tune->buf_capacity > 0))) {
         void *args[] = {&a, &src};
         return launch(ctx, "sssp_small", reinterpret_cast<const void *>(&sssp_small), dim3(1), dim3(kSmallBlock), args,
