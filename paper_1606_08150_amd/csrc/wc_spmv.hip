@@ -22,7 +22,8 @@
 //           g (1..64) and one wave sums 64 / g rows of a bin at once; a row
 //           longer than 64 * items_per_lane is split into chunks of that size,
 //           one wave each, and its chunk partials are combined in chunk order.
-//           A counting pass sizes the bins before the parent pass fills them.
+//           A bin's buffer holds every row, so the parent reserves places as it goes;
+//           a small matrix runs in one launch (spmv_small).
 //   flat  - every row is summed by its own lane.
 // All sums are fp32 fused multiply-adds whose order depends only on the row
 // length, the mode and the tune, so results are bitwise reproducible.  Every
