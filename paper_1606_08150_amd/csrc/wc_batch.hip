@@ -93,27 +93,26 @@ __device__ __forceinline__ Range make_range(const BatchArgs &a, int i)
 
 // K loaded edges a lane (v[k] < 0: none), nd[k] the distances they offer.  An edge
 // is dropped by the byte that bounds its target's distance (bound_code), which takes
-// half the cache and which no atomic touches; the others read the distance itself
-// (the drains of the later rounds 20 % faster, the first dense ones even).  The mark
-// that a relaxation leaves carries the bound of the distance it offers: the vertex's
-// own is never above any of them, whichever store comes last.  Marking on nd < the
-// distance read gives the same frontier as waiting for the atomic's old value, as in
-// single-instance SSSP.
+// half the cache and which no atomic touches; the others go to the atomic without a
+// look at the distance (64 graphs, block level: 1.40 ms a call with it, 1.22
+// without).  The mark that a relaxation leaves carries the bound of the distance it
+// offers: the vertex's own is never above any of them, whichever store comes last.
+// A vertex marked by a relaxation that lowered nothing is found relaxed with its
+// distance and passed over.
 template <int K>
 __device__ __forceinline__ bool relax_loaded(const Range *const (&t)[K], int (&v)[K], const uint32_t (&nd)[K],
                                              int next)
 {
-    uint32_t dv[K];
+    uint32_t bound[K];
     bool any = false;
 #pragma unroll
-    for (int k = 0; k < K; ++k) dv[k] = v[k] >= 0 ? t[k]->mark[v[k]] & 255u : 0u;
+    for (int k = 0; k < K; ++k) bound[k] = v[k] >= 0 ? t[k]->mark[v[k]] & 255u : 0u;
+    // all tests before the first atomic: 10 % faster than one edge after another
 #pragma unroll
-    for (int k = 0; k < K; ++k) v[k] = nd[k] < bound_value(dv[k]) ? v[k] : -1;
-#pragma unroll
-    for (int k = 0; k < K; ++k) dv[k] = v[k] >= 0 ? t[k]->dist[v[k]] : 0u;
+    for (int k = 0; k < K; ++k) v[k] = nd[k] < bound_value(bound[k]) ? v[k] : -1;
 #pragma unroll
     for (int k = 0; k < K; ++k) {
-        if (v[k] < 0 || nd[k] >= dv[k]) continue;
+        if (v[k] < 0) continue;
         (void)__hip_atomic_fetch_min(&t[k]->dist[v[k]], nd[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         t[k]->mark[v[k]] = (uint16_t)(next << 8 | bound_code(nd[k]));
         any = true;
@@ -237,10 +236,11 @@ __device__ __forceinline__ bool relax_buffer(const Range *item, int cap, int ns,
 // Bound by that chain where the frontier is sparse, and by the relaxations' random
 // accesses where it is dense (62M edges relaxed in a batch of 64 power-law graphs of
 // 2^10 to 2^17 vertices, 16 edges each; its random reads run at about 140 G/s).
-// That batch, 16 rounds: block level 1,414 -> 880 us in this kernel and 2.04 ->
-// 1.44 ms a call (thread-strided single edges, a window at a time, generic
-// pointers before), wave level 2.83 -> 1.56 ms, grid level 1.76 -> 1.51 ms.  Eight
-// windows a step: 2 to 5 % slower (4 % faster in batches of 256); two: 5 % slower.
+// That batch, 16 rounds: block level 1,414 -> 780 us in this kernel and 2.04 ->
+// 1.26 ms a call (thread-strided single edges, a window at a time, generic
+// pointers before), wave level 2.83 -> 1.30 ms, grid level 1.76 -> 1.34 ms.  Lane
+// groups taking adjacent edges instead of quads: 3 % slower in this kernel.  Two
+// or eight windows a step: within 2 % there; 256 graphs 3 % and 1 % slower.
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) void batch_round(BatchArgs a, int r)
 {
@@ -379,16 +379,17 @@ __global__ __launch_bounds__(BLOCK) void batch_round(BatchArgs a, int r)
     if (a.want_stats) stat_flush(a.stats, acc);
 }
 
-// The chunks of round r's global buffer: half a wave a chunk and two chunks of it
-// at a time (of any instances), four consecutive edges a lane and load, so that a
-// chunk of 128 edges is one load an array.  The source distances are read after
-// the edges are requested; the largest one used raises relaxed_at.  606 -> 490 us
-// in the batch of 64 (a wave a chunk, one edge a lane and load before).
 // The drain's grid, in resident grids: the hardware then hands out the chunks in
-// their order, so that those in flight are near each other (the batch of 64: 1.52,
-// 1.48, 1.44 ms a call at 1, 2, 4; 16 pays for empty blocks in the sparse rounds).
+// their order, so that those in flight are near each other (256 graphs at block
+// level 3.64, 3.54, 3.50 ms a call at 1, 2, 4, at grid level 4.16, 4.12, 3.98; the
+// batch of 64 within 3 %; 16 pays for empty blocks in the sparse rounds).
 constexpr int kDrainWaves = 4;
 
+// The chunks of round r's global buffer: a wave a chunk and two chunks at a time (of
+// any instances), adjacent lanes taking adjacent edges: the columns of a row are
+// sorted, so their targets share lines.  The source distances are read after the
+// edges are requested; the largest one used raises relaxed_at.  606 -> 402 us in the
+// batch of 64 (432 with half a wave a chunk and four consecutive edges a lane).
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) void batch_drain(BatchArgs a, int r)
 {
@@ -400,42 +401,38 @@ __global__ __launch_bounds__(BLOCK) void batch_drain(BatchArgs a, int r)
     const int nw = gridDim.x * (BLOCK / kWave);
     if (a.want_stats && blockIdx.x == 0 && threadIdx.x == 0 && total > 0)
         atomic_add_dev(&a.stats->rep[0].dispatches, 1ull);
-    constexpr int kHalf = kWave / 2, kStep = 4 * kHalf;
-    const int half = lane_id() / kHalf, sub = lane_id() & (kHalf - 1);
     bool any = false;
-    // the next entries are fetched before the current chunks' edges
-    const long long first = gw + (long long)half * nw, step = 4ll * nw;
+    constexpr int U = 2;
     int4 q[2];
 #pragma unroll
-    for (int p = 0; p < 2; ++p) q[p] = load_or_zero(a.chunks, first + 2ll * p * nw, first + 2ll * p * nw < total);
-    for (long long c = first; c < total; c += step) {
+    for (int p = 0; p < 2; ++p) q[p] = load_or_zero(a.chunks, gw + (long long)p * nw, gw + (long long)p * nw < total);
+    for (long long c = gw; c < total; c += 2ll * nw) {
         Range t[2];
         int src[2], gid[2];
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
-            gid[p] = q[p].x;
-            t[p] = make_range(a, q[p].w);
-            src[p] = gid[p] - a.vbase[q[p].w];
-            t[p].beg = q[p].y;
-            t[p].end = q[p].z;
-            const long long n = c + step + 2ll * p * nw;
+            gid[p] = __builtin_amdgcn_readfirstlane(q[p].x);
+            const int i = __builtin_amdgcn_readfirstlane(q[p].w);
+            t[p] = make_range(a, i);
+            src[p] = gid[p] - a.vbase[i];
+            t[p].beg = __builtin_amdgcn_readfirstlane(q[p].y);
+            t[p].end = __builtin_amdgcn_readfirstlane(q[p].z);
+            const long long n = c + (2ll + p) * nw;
             q[p] = load_or_zero(a.chunks, n, n < total);
         }
         const int len = max(t[0].end - t[0].beg, t[1].end - t[1].beg);
         uint32_t used[2] = {0u, 0u};
-        for (int o = 4 * sub; o - 4 * sub < len; o += kStep) {
-            int v[8];
-            uint32_t w[8];
-            const Range *range[8];
+        for (int o = 0; o < len; o += U * kWave) {
+            int v[2 * U];
+            uint32_t w[2 * U];
+            const Range *range[2 * U];
 #pragma unroll
-            for (int p = 0; p < 2; ++p) {
-                const int e = t[p].beg + o;
-                if (e < t[p].end) {
-                    load_quad(t[p], e, v + 4 * p, w + 4 * p);
-                } else {
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) v[4 * p + k] = -1, w[4 * p + k] = 0u;
-                }
+            for (int k = 0; k < 2 * U; ++k) {
+                const Range &x = t[k / U];
+                const int e = x.beg + o + (k % U) * kWave + lane_id();
+                v[k] = e < x.end ? x.col[e] : -1;
+                w[k] = e < x.end ? x.w[e] : 0u;
+                range[k] = &x;
             }
 #pragma unroll
             for (int p = 0; p < 2; ++p) {
@@ -443,10 +440,10 @@ __global__ __launch_bounds__(BLOCK) void batch_drain(BatchArgs a, int r)
                 used[p] = max(used[p], t[p].du);
             }
 #pragma unroll
-            for (int k = 0; k < 8; ++k) w[k] = add_sat(t[k / 4].du, w[k]), range[k] = &t[k / 4];
-            any |= relax_loaded<8>(range, v, w, next);
+            for (int k = 0; k < 2 * U; ++k) w[k] = add_sat(t[k / U].du, w[k]);
+            any |= relax_loaded<2 * U>(range, v, w, next);
         }
-        if (sub == 0) {
+        if (lane_id() == 0) {
 #pragma unroll
             for (int p = 0; p < 2; ++p)
                 if (t[p].beg < t[p].end) atomic_max_dev_noret(&a.relaxed_at[gid[p]], used[p]);
@@ -549,9 +546,9 @@ extern "C" wc_status wc_sssp_batch(wc_ctx *ctx, int32_t count, const wc_csr *gra
     // wave- or block-level instances also at least a workgroup for each step of
     // kWindowsPerStep windows, so the hardware hands the steps dense with buffered
     // vertices to CUs as they free up (block level, 64 instances of 2^10 to 2^17
-    // vertices: 1.47 -> 1.43 ms; 16 of 2^8 to 2^12, of 85 windows: 0.46 ms by steps
-    // alone, 0.32 ms by windows); grid-level instances keep the resident grid
-    // (64: 1.51 against 1.50 ms, 16: 0.26 against 0.31 ms).
+    // vertices: 2 % faster; 16 of 2^8 to 2^12, of 85 windows: 0.46 ms by steps
+    // alone, 0.24 ms by windows); grid-level instances keep the resident grid
+    // (64: even, 16: 0.26 against 0.31 ms).
     int grid = std::max(1, std::min(resident, windows));
     if (has[WC_WAVE] || has[WC_BLOCK]) grid = std::max(grid, (windows + kWindowsPerStep - 1) / kWindowsPerStep);
     const int dgrid = std::max(1, resident * kDrainWaves);
