@@ -760,12 +760,13 @@ __global__ void tree_zero_out(TreeArgs a)
 //   tree_fold_climb  - from the finished nodes upward: each folds into its
 //     parent with one atomic, and the child that completes a node carries on
 //     with it.
-// Bound by the gathers of the children's ranges (shuffled ids: a line of 128
-// bytes a child entry, 45 of the 84 us of the tile pass on the 2^22-node tree)
-// and by the round trips of the climb (one a level, two for heights); the level
+//   tree_fold_inner  - before it, for a large tree: which nodes have children.
+// Bound by the gathers of the children's bits (in smaller trees ranges: shuffled
+// ids, a line of 128 bytes a child entry; 84 -> 48 us by the bits in the tile pass
+// of the 2^22-node tree) and by the round trips of the climb (one a level, two for heights); the level
 // schedule it replaces paid two launches of 6 to 110 us a level.
 // Descendants of 2^22-node random trees of 9 to 23 levels: 485 to 917 -> 104 to
-// 129 us; heights of 64 trees of 2^10 to 2^17 nodes in one call: 575 -> 99 us.
+// 129 us, with the bits 96 for the deep ones; heights of 64 trees of 2^10 to 2^17 nodes in one call: 575 -> 99 us.
 constexpr int kTile = 2048;        // work-list entries (child entries and nodes) a tile
 constexpr int kTileBlock = 256;
 constexpr int kTileReady = kTile / 2 + 1;  // a final node brings a child entry and, but for the last one, itself
@@ -790,6 +791,7 @@ struct FoldArgs {
     int *ready;        // [tiles * kTileReady]: final nodes of each tile
     int *ready_count;  // [tiles]
     int2 *carry;       // [tiles]: (node whose entries began in an earlier tile or -1, its leaves here)
+    unsigned long long *inner;  // a large single tree: bit v set where node v has children; else nullptr
 };
 
 // The tree of a tile, its arrays known to be global memory.
@@ -898,7 +900,10 @@ __global__ __launch_bounds__(kTileBlock) void tree_fold_tiles(FoldArgs a)
     for (int i = tid; i <= nn; i += kTileBlock) s_ptr[i] = t.child_ptr[p0 + i];
     for (int i = tid; i < nn; i += kTileBlock) s_leaf[i] = 0;
 #pragma unroll
-    for (int k = 0; k < E; ++k) f[k] = c[k] >= 0 ? t.child_ptr[c[k] + 1] - t.child_ptr[c[k]] : 0;
+    for (int k = 0; k < E; ++k) {
+        if (!BATCH && a.inner) f[k] = c[k] >= 0 ? static_cast<int>(a.inner[c[k] / 64] >> (c[k] & 63)) & 1 : 0;
+        else f[k] = c[k] >= 0 ? t.child_ptr[c[k] + 1] - t.child_ptr[c[k]] : 0;
+    }
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < E; ++k) {
@@ -1013,13 +1018,40 @@ TreeKernels<OP, BLOCK> kernels_for(wc_mode mode)
 // Fold tiles over one tree or a batch: workspace of the two kernels.
 struct FoldPlan {
     long long nodes = 0, tiles = 0;
+    long long inner = 0;    // words of the bits of a large single tree
     size_t desc_bytes = 0;  // batch: descriptors and the tree of each tile
     size_t bytes() const
     {
         return padded(nodes * 8) + padded(nodes * 4) + padded(tiles * kTileReady * 4) + padded(tiles * 4) +
-               padded(tiles * 8) + padded(desc_bytes);
+               padded(tiles * 8) + padded(inner * 8) + padded(desc_bytes);
     }
 };
+
+// The nodes with children of a tree, a bit each: the tile pass then gathers from n /
+// 8 bytes, which an XCD's cache holds, instead of a line of child_ptr a child entry.
+// Bound by the copy rate (10 us at 2^22 nodes, 33 MB read) and its launch.  From 2^20 nodes:
+// heights of random trees without / with it 82.6 / 82.9 us at 1,000,000 nodes, 92.6 /
+// 90.4 at 1,500,000, 109 / 101 at 2^21, 162 / 130 at 2^22.
+constexpr int kInnerBlock = 256;
+constexpr int kInnerWords = 4;  // words of 64 nodes a wave
+constexpr int kInnerNodes = 1 << 20;
+__global__ __launch_bounds__(kInnerBlock) void tree_fold_inner(FoldArgs a)
+{
+    const long long w0 = (blockIdx.x * (kInnerBlock / kWave) + threadIdx.x / kWave) * (long long)kInnerWords;
+    int beg[kInnerWords], end[kInnerWords];
+#pragma unroll
+    for (int k = 0; k < kInnerWords; ++k) {
+        const long long v = (w0 + k) * kWave + lane_id();
+        beg[k] = v < a.one.n ? a.one.child_ptr[v] : 0;
+        end[k] = v < a.one.n ? a.one.child_ptr[v + 1] : 0;
+    }
+#pragma unroll
+    for (int k = 0; k < kInnerWords; ++k) {
+        const unsigned long long bits = __ballot(end[k] > beg[k]);
+        if (lane_id() == 0 && (w0 + k) * kWave < a.one.n) a.inner[w0 + k] = bits;
+    }
+}
+
 
 FoldPlan plan_fold(const TreeArgs &a, const std::vector<TreeInst> *batch)
 {
@@ -1030,6 +1062,7 @@ FoldPlan plan_fold(const TreeArgs &a, const std::vector<TreeInst> *batch)
     };
     if (!batch) {
         add(a.n);
+        if (a.n > kInnerNodes) f.inner = (a.n + kWave - 1) / kWave;
     } else {
         for (const TreeInst &t : *batch) add(t.n);
         f.desc_bytes = padded(sizeof(FoldTree) * batch->size()) + sizeof(int) * (size_t)f.tiles;
@@ -1051,6 +1084,14 @@ wc_status run_fold(wc_ctx *ctx, const TreeArgs &t, const FoldPlan &f, const std:
     chain_break(ctx);
     if (!batch) {
         a.one = FoldTree{t.child_ptr, t.child, t.out, t.n, 0, 0};
+        if (f.inner) {
+            a.inner = pool_take<unsigned long long>(ctx, f.inner);
+            void *iargs[] = {&a};
+            const long long waves = (f.inner + kInnerWords - 1) / kInnerWords, per = kInnerBlock / kWave;
+            wc_status st = launch(ctx, "tree_fold_inner", reinterpret_cast<const void *>(&tree_fold_inner),
+                                  dim3((unsigned)((waves + per - 1) / per)), dim3(kInnerBlock), iargs, stream);
+            if (st != WC_OK) return st;
+        }
     } else {
         char *dev = pool_take<char>(ctx, f.desc_bytes);
         std::vector<char> host(f.desc_bytes);
