@@ -183,6 +183,8 @@ wc_status wc_ctx_destroy(wc_ctx *ctx);
  * unreachable.  Frontier-driven rounds: every vertex whose distance improved is
  * expanded in the next round; a frontier vertex with more than `threshold`
  * out-edges is consolidated per `mode`, a lighter one relaxes its edges inline.
+ * WC_GRID with the library's tune and no stats runs a graph of up to 8,192
+ * vertices and 4 to 131,072 edges in one launch (one workgroup, no waiting).
  * dist[n] is written entirely.  Distances must stay below UINT32_MAX. */
 wc_status wc_sssp(wc_ctx *ctx, const wc_csr *g, const uint32_t *w, int32_t src, uint32_t *dist, wc_mode mode,
                   const wc_tune *tune, hipStream_t stream, wc_stats *stats);
