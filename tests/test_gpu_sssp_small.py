@@ -6,6 +6,7 @@ distances; against the oracle and the general path (a caller's threshold),
 exactly."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 import synth
@@ -59,3 +60,22 @@ def test_small_graphs(ctx):
                     assert np.array_equal(d, oracle.sssp_dijkstra(g.row_ptr, g.col, w, src)), (name, top, src)
         say(f"small bfs {name}")
         assert np.array_equal(dev_to_u32(ctx.bfs(dg, 0)), oracle.bfs(g.row_ptr, g.col, 0)), name
+
+
+@pytest.mark.parametrize("n", [4097, 10007])
+@pytest.mark.parametrize("off", [1, 2, 3])
+def test_arrays_at_any_element(ctx, n, off):
+    """Columns, weights and distances that start at any element of an allocation,
+    on both paths; nothing is written beside the distances."""
+    g = with_edges(n, 5 * n + 1, n)
+    w = np.random.default_rng(off).integers(1, 1000, g.m, dtype=np.uint32)
+    col = torch.zeros(g.m + 8, dtype=torch.int32, device="cuda")
+    wt, out = torch.zeros_like(col), torch.full((n + 8,), 77, dtype=torch.int32, device="cuda")
+    col[off:off + g.m] = torch.from_numpy(g.col).cuda()
+    wt[off:off + g.m] = u32_to_dev(w)
+    dg = wc.DeviceCSR(n, torch.from_numpy(g.row_ptr).cuda(), col[off:off + g.m])
+    say(f"sssp arrays at element {off} n={n}")
+    ctx.sssp(dg, wt[off:off + g.m], 3, out=out[off:off + n])
+    torch.cuda.synchronize()
+    assert np.array_equal(dev_to_u32(out[off:off + n]), oracle.sssp_dijkstra(g.row_ptr, g.col, w, 3))
+    assert (out[:off] == 77).all() and (out[off + n:] == 77).all()
