@@ -313,8 +313,10 @@ __global__ __launch_bounds__(BLOCK) void batch_round(BatchArgs a, int r)
                 mode = deg > d.threshold ? d.mode : WC_FLAT;
                 // a wave's or block's own child keeps items of up to one chunk;
                 // longer ones go to the grid-wide drain (the KC_X rule of
-                // Sec. IV.E: a warp's or block's child gets many blocks)
-                if ((mode == WC_WAVE || mode == WC_BLOCK) && deg > chunk) mode = WC_GRID;
+                // Sec. IV.E: a warp's or block's child gets many blocks), and so
+                // do those of an instance of fewer than four edges, which the
+                // children's loads of four would pass the ends of
+                if ((mode == WC_WAVE || mode == WC_BLOCK) && (deg > chunk || t.m < 4)) mode = WC_GRID;
                 // wave, block and inline work use this reading; grid chunks raise
                 // the value from 0 in the drain (or it stays du on overflow)
                 if (deg > 0 && mode != WC_GRID) a.relaxed_at[g] = t.du;
@@ -531,7 +533,9 @@ extern "C" wc_status wc_sssp_batch(wc_ctx *ctx, int32_t count, const wc_csr *gra
         total += g.n;
         if (mode == WC_GRID) cap += g.n + g.m / chunk + 1;
         // wave and block levels hand vertices with more than one chunk of edges
-        // (at most 2 deg / chunk chunks each) to the grid path
+        // (at most 2 deg / chunk chunks each) to the grid path, and in an instance
+        // of fewer than four edges the one vertex above a threshold (two edges or
+        // more), a chunk
         if (mode == WC_WAVE || mode == WC_BLOCK) {
             has[WC_GRID] = 1;
             cap += 2 * (g.m / chunk) + 1;
