@@ -468,7 +468,7 @@ __global__ __launch_bounds__(kNarrowBlock) void color_narrow(ColorArgs a, int st
     __shared__ int2 s_list[2][kNarrowList];
     __shared__ int s_ready[kNarrowBlock];
     __shared__ int s_next[2], s_found[2];  // chunks of a list, vertices readied
-    __shared__ int s_tmp[2 * NW], s_readied, s_spill, s_bad;
+    __shared__ int s_tmp[2 * NW], s_readied, s_spill, s_listed, s_bad;
     __shared__ unsigned int s_wait[kNarrowN / 2];
     const int tid = threadIdx.x, lane = lane_id();
     const int wid = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -483,6 +483,7 @@ __global__ __launch_bounds__(kNarrowBlock) void color_narrow(ColorArgs a, int st
     if (tid == 0) {
         s_next[0] = fits ? nchunks : 0;
         s_found[0] = s_readied = s_spill = s_bad = 0;
+        s_listed = kNarrowList;
     }
     if (fits && nchunks > 0) {
         bool large = false;
@@ -537,9 +538,9 @@ __global__ __launch_bounds__(kNarrowBlock) void color_narrow(ColorArgs a, int st
                 }
             } else {
                 // more than the list holds (the round is too large anyway): the vertex
-                // to memory, empty entries in its place
-                for (int c = slot + sub; c < kNarrowList; c += kNarrowGroup) next[c] = make_int2(0, 0);
+                // to memory; the list ends where the first such vertex would begin
                 if (sub == 0) {
+                    atomicMin(&s_listed, slot);
                     const int q = atomicAdd(&s_spill, 1);
                     if (q < a.n) a.queue1[q] = v;
                 }
@@ -572,9 +573,10 @@ __global__ __launch_bounds__(kNarrowBlock) void color_narrow(ColorArgs a, int st
             a.wait[2 * i] = (int)(q & 0xffffu);
             if (2 * i + 1 < a.n) a.wait[2 * i + 1] = (int)(q >> 16);
         }
-        // the list becomes the chunk buffer of its round
+        // the list becomes the chunk buffer of its round: the chunks of each of its
+        // vertices once, which the buffer holds
         int4 *out = (r & 1) ? a.chunks1 : a.chunks;
-        chunks = min(count, kNarrowList);
+        chunks = min(count, s_listed);
         if (tid < chunks) out[tid] = make_int4(0, s_list[k & 1][tid].x, s_list[k & 1][tid].y, 0);
         const int spilled = min(s_spill, a.n);
         for (int i0 = 0; i0 < spilled; i0 += kNarrowBlock) {
