@@ -549,15 +549,26 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(HOT ? 4 :
 // and its waves take the same tasks as the grid-wide child (lane groups per
 // row, chunks of the split rows with their partials in LDS, the light rows one
 // lane each), so every sum has the order of the general path.  A workgroup's
-// rows lie a grid apart (hubs often have neighbouring ids).  Rule: up to
-// kSmallNnz entries; 8 rows fill the lane groups of seven bins worse than all
-// rows of the matrix do.  R-MAT, 16 entries a row, this kernel / the general
-// path: 4,096 rows 9.6 / 16.6 us (23.5 before), 16,384 rows (2^18 entries) 13.1
-// / 16.6, 32,768 rows 20.0 / 17.3, 131,072 rows 77 / 26.
+// rows lie a grid apart (hubs often have neighbouring ids).  Rule (small_product):
+// up to kSmallNnz entries, for 8 rows fill the lane groups of seven bins worse
+// than all rows of the matrix do.  R-MAT, 16 entries a row, this kernel / the
+// general path: 4,096 rows 9.6 / 16.6 us (23.5 before), 16,384 rows (2^18 entries)
+// 13.1 / 16.6, 32,768 rows 20.0 / 17.3, 131,072 rows 77 / 26.  Up to kSmallN rows,
+// for the workgroups are as many as the rows ask, filled or not: 2^18 entries in
+// 32,768 rows 12.4 / 13.4 us, in 40,000 14.0 / 13.8, in 2^20 233 / 13.  And a row
+// is one workgroup's, a third of a us per thousand entries beyond the first ten
+// thousand: a row of a matrix that has an entry once is no longer than n, so a
+// matrix of more than n^2 entries is only taken while one row could hold them all
+// (64 rows, all entries in one: 2^15 17 / 13 us, 2^16 31 / 13, 2^18 116 / 21).
 // Bound by launch and memory latency.
 constexpr int kSmallBlock = 512;
 constexpr int kSmallRows = 8;
 constexpr int kSmallNnz = 1 << 18;
+constexpr int kSmallN = 1 << 15;
+bool small_product(long long n, long long m)
+{
+    return n <= kSmallN && m <= kSmallNnz && m <= std::max<long long>(kSmallN, n * n);
+}
 constexpr int kSmallChunk = 512;  // smallest chunk it is used with
 __global__ __launch_bounds__(kSmallBlock) void spmv_small(SpmvArgs a)
 {
@@ -821,7 +832,7 @@ wc_status spmv_shape(int num_cus, const wc_csr *g, const float *val, wc_mode mod
     // one launch for a small matrix, where the launch shape, the threshold and
     // the buffers are the library's choice and nothing is counted
     p->small = mode == WC_GRID && !hot && !want_stats && !cfg.own_shape && !(tune && tune->threshold > 0) &&
-               cfg.buf_capacity <= 0 && cfg.driver == 0 && m <= kSmallNnz && chunk >= kSmallChunk;
+               cfg.buf_capacity <= 0 && cfg.driver == 0 && small_product(n, m) && chunk >= kSmallChunk;
     return WC_OK;
 }
 
