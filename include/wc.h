@@ -353,8 +353,8 @@ wc_status wc_sssp_batch(wc_ctx *ctx, int32_t count, const wc_csr *graphs, const 
  * product, kernels and summation order as wc_spmv with the same mode and tune
  * (so bit-identical results), but no context, no pool and no stats.  The
  * grid-mode workspace lives in one fixed device array of
- * WC_SPMV_NOALLOC_SCRATCH_BYTES per device, held from the first call on that
- * device until the process ends; the call makes no hipMalloc, hipFree or other
+ * WC_SPMV_NOALLOC_SCRATCH_BYTES per device (and 2 MiB for counters), held from
+ * the first call on that device until the process ends; the call makes no hipMalloc, hipFree or other
  * allocating call.  Grid mode is given 52 n + 20 m / (64 * items_per_lane)
  * + 72 ceil(n / block_threads) bytes (n up to about 1.2 million at m = 16 n
  * with the defaults); a call whose workspace could exceed the array returns

@@ -1218,7 +1218,10 @@ extern "C" wc_status wc_spmv_hot(wc_ctx *ctx, const wc_csr *a_hot, int32_t hot, 
 // hipGetSymbolAddress returns for it, taken once per device on the first call
 // made with that device current.
 
-static __device__ __align__(256) unsigned char scratch[WC_SPMV_NOALLOC_SCRATCH_BYTES];
+// The documented bytes, which decide what is refused, and room for the counters
+// (spmv_noalloc_bound).
+constexpr size_t kNoAllocScratch = (size_t)WC_SPMV_NOALLOC_SCRATCH_BYTES + (2u << 20);
+static __device__ __align__(256) unsigned char scratch[kNoAllocScratch];
 
 namespace wc {
 namespace {
@@ -1232,18 +1235,16 @@ struct NoAllocDevice {
 std::mutex g_noalloc_mu;
 NoAllocDevice g_noalloc[kMaxDevices];
 
-// Workspace bound from n, m and the tune alone (the documented one, in grid mode
-// an upper bound of what the kernels use but for a few bytes), so oversized
-// calls are refused before any HIP call is made.
+// Workspace bound from n, m and the tune alone (the documented one), so oversized
+// calls are refused before any HIP call is made.  Rows, chunks and split rows as
+// they are documented: in grid mode 16 bytes a row for the bins, which hold row
+// ids in four regions of up to n now, and 72 bytes a block.  The counters, each
+// on a line of its own, are not in it: the array has room for them beside it.
 size_t spmv_noalloc_bound(const wc_csr *g, const SpmvPlan *p)
 {
-    size_t bytes = spmv_workspace_bytes(p);
-    if (p->mode == WC_GRID) {
-        const size_t n = (size_t)g->n, blocks = (n + p->cfg.block - 1) / p->cfg.block;
-        bytes = std::max(bytes, 2 * padded(n * 16) + padded(p->cap * 16) + padded(p->cap * 4) +
-                                    2 * padded(blocks * 36) + padded(36));
-    }
-    return bytes + padded(sizeof(DevStats));
+    const size_t n = (size_t)g->n, blocks = p->mode == WC_GRID ? (n + p->cfg.block - 1) / p->cfg.block : 1;
+    return 2 * padded(blocks * 36) + padded(36) + padded((p->mode == WC_GRID ? n : 1) * 16) + padded(p->cap * 16) +
+           padded(p->cap * 4) + padded(p->mcap * 16) + padded(sizeof(DevStats));
 }
 
 }  // namespace
@@ -1266,7 +1267,8 @@ extern "C" wc_status wc_spmv_noalloc(const wc_csr *g, const float *val, const fl
     wc_status st = spmv_shape(1, g, val, mode, tune, false, &p);
     if (st != WC_OK) return st;
     const size_t bound = spmv_noalloc_bound(g, &p);
-    if (bound > (size_t)WC_SPMV_NOALLOC_SCRATCH_BYTES)
+    if (bound > (size_t)WC_SPMV_NOALLOC_SCRATCH_BYTES ||
+        spmv_workspace_bytes(&p) + padded(sizeof(DevStats)) > kNoAllocScratch)  // (the second never without the first)
         return fail(WC_EINVAL, "wc_spmv_noalloc: the workspace (" + std::to_string(bound) +
                                    " bytes) exceeds the fixed scratch of " +
                                    std::to_string((size_t)WC_SPMV_NOALLOC_SCRATCH_BYTES) + " bytes");
