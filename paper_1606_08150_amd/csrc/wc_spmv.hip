@@ -76,9 +76,10 @@ struct SpmvArgs {
     long long bin_off[kBins + 1];
     long long rows_cap;  // driver 2: entries of `basic`
     int4 *basic;       // driver 2: (row, begin, end, 0)
-    int4 *chunks;      // (row, begin, end, entry in multi)
+    int4 *chunks;      // (what counts the chunk, begin, end, entry in multi), see put_chunk
     long long chunk_cap;
-    int4 *multi;       // (row, first chunk, chunk count, chunks still to be summed)
+    int *groups;       // chunks still to be summed of the groups of long rows
+    int4 *multi;       // (row, first chunk, chunk count, chunks or groups still to be summed)
     long long multi_cap;
     float *partials;   // one per chunk slot
     DevStats *stats;
@@ -163,6 +164,46 @@ __device__ __forceinline__ long long bin_entry(const SpmvArgs &a, int b, int i)
     return b & 1 ? a.bin_off[b] - i : a.bin_off[b] + i;
 }
 
+// Chunks of split rows.  A row's entry in multi counts its chunks that are still
+// to be summed or, for a row of more than kGroup chunks, its groups: the chunks
+// with entries in one run of kGroup entries of the buffer, counted in `groups`.
+// Such a row reaches beyond a run, so a run has two of them at most, one from its
+// start on and one that begins later, with a count each.
+constexpr int kGroup = 64;
+constexpr int kGroupPad = 8;  // counts of a run (two are used): four runs a line
+enum { kRow = 0, kGroupOf = 1 };  // chunks[].x: counted by the row; or by count x - kGroupOf of the run; -1: empty
+
+// The group of a row of n chunks from `first` that has the entry `slot`: where its
+// count is, and what that starts from.
+__device__ __forceinline__ int group_of(int first, int slot) { return first > (slot & ~(kGroup - 1)) ? 1 : 0; }
+__device__ __forceinline__ long long group_index(int slot, int which)
+{
+    return (long long)(slot / kGroup) * kGroupPad + which;
+}
+__device__ __forceinline__ int group_count(int first, int n, int slot)
+{
+    const long long run = slot & ~(kGroup - 1);
+    return (int)(min((long long)first + n, run + kGroup) - max((long long)first, run));
+}
+// What the row's entry in multi counts.
+__device__ __forceinline__ int row_count(int first, int n)
+{
+    return n <= kGroup ? n : (first + n - 1) / kGroup - first / kGroup + 1;
+}
+
+// Chunk c of a row [beg, end) of n chunks whose first has the entry `first`.
+__device__ __forceinline__ void put_chunk(const SpmvArgs &a, int first, int n, int c, int beg, int end, int entry)
+{
+    const int slot = first + c, cb = beg + c * a.chunk;
+    int by = kRow;
+    if (n > kGroup) {
+        const int which = group_of(first, slot);
+        by = kGroupOf + which;
+        if (c == 0 || slot % kGroup == 0) a.groups[group_index(slot, which)] = group_count(first, n, slot);
+    }
+    a.chunks[slot] = make_int4(by, cb, min(end, cb + a.chunk), entry);
+}
+
 template <int BLOCK>
 struct SpmvBlockBuf {
     int row[BLOCK];  // buffered rows, laid out by bin
@@ -196,13 +237,10 @@ __device__ __forceinline__ void spill_rows(const SpmvArgs &a, int r, int beg, in
         const int b = __builtin_ctzll(m);
         m &= m - 1;
         const int s0 = readlane(slot, b), n0 = readlane(nch, b), rb = readlane(beg, b), re = readlane(end, b);
-        const int rr = readlane(r, b), rm = readlane(mslot, b);
-        for (int c = lane_id(); c < n0; c += kWave) {
-            const int cb = rb + c * a.chunk;
-            a.chunks[s0 + c] = make_int4(rr, cb, min(re, cb + a.chunk), rm);
-        }
+        const int rm = readlane(mslot, b);
+        for (int c = lane_id(); c < n0; c += kWave) put_chunk(a, s0, n0, c, rb, re, rm);
     }
-    if (fits) a.multi[mslot] = make_int4(r, slot, nch, nch);
+    if (fits) a.multi[mslot] = make_int4(r, slot, nch, row_count(slot, nch));
     if (nch > 0 && !fits) {
         for (int c = 0; c < nch; ++c)
             if ((long long)slot + c < a.chunk_cap) a.chunks[slot + c] = make_int4(-1, 0, 0, 0);
@@ -400,12 +438,12 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(8))) void
 #pragma unroll
                 for (int d = kWave / 2; d >= 1; d >>= 1) own += __shfl(pre, own + d, kWave) <= j ? d : 0;
                 const int c = j - __shfl(pre, own, kWave);
-                const int cb = __shfl(rb, own, kWave) + c * a.chunk, e0 = __shfl(re, own, kWave);
-                const int s0 = __shfl(slot, own, kWave), rr = __shfl(r, own, kWave), rm = __shfl(mslot, own, kWave);
-                if (j < chunks) a.chunks[s0 + c] = make_int4(rr, cb, min(e0, cb + a.chunk), rm);
+                const int b0 = __shfl(rb, own, kWave), e0 = __shfl(re, own, kWave), n0 = __shfl(nch, own, kWave);
+                const int s0 = __shfl(slot, own, kWave), rm = __shfl(mslot, own, kWave);
+                if (j < chunks) put_chunk(a, s0, n0, c, b0, e0, rm);
             }
             if (fits) {
-                a.multi[mslot] = make_int4(r, slot, nch, nch);
+                a.multi[mslot] = make_int4(r, slot, nch, row_count(slot, nch));
             } else if (split) {
                 // buffer full: mark the reserved slots that exist as empty and sum
                 // the row inline (fallback); no chunk refers to its split-row entry
@@ -439,27 +477,52 @@ struct DrainLds {
 // entries.
 // Post-work of split rows, by the wave whose chunk is the row's last one to be
 // done: the row's partials summed in chunk order, whoever does it.  A wave's
-// partials have reached memory (the wait) before it lowers the rows' counts,
-// and the counts go down by atomics alone, so the wave that takes one to zero
-// finds every partial.  The counts are lowered between the wave's chunks and
+// partials have reached memory (the wait) before it lowers the counts of their
+// rows or groups; the wave that takes a group's to zero lowers the row's after
+// that; and the counts go down by atomics alone, so the wave that takes a row's to
+// zero finds every partial.  The counts are lowered between the wave's chunks and
 // its other tasks, which hide the round trips (counting after every chunk cost
 // 17 us of the scale-22 product, this 7, a kernel of its own a launch), and are
 // left as they were found, for the next product on the same buffers.
+// Groups, for atomics on one line take turns: with a count a row only, a product
+// with six rows of 2^19 entries took 89 us in grid mode (chunks of 512) and 171 in
+// wave mode (128), one row of 2^20 entries 55 and 142; now 31 and 45, 33 and 36.
 // Bound by the gathers of x, a line request a lane: 62M of them in 433 us on the
 // scale-22 graph, a bare gather of its 67M columns 385 us.
-__device__ __forceinline__ void combine_rows(const SpmvArgs &a, int mi, int left)
+constexpr int kPartials = 8;  // partials of a long row in flight per lane
+__device__ __forceinline__ float load_partial(const SpmvArgs &a, int k)
+{
+    return __hip_atomic_load(&a.partials[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// mi: the lane's split-row entry (-1: none), by: what counts its chunk, left: that
+// count before it was lowered.
+__device__ __forceinline__ void combine_rows(const SpmvArgs &a, int mi, int by, int left)
 {
     asm volatile("" : : "v"(left) : "memory");
-    for (uint64_t m = __ballot(left == 1); m; m &= m - 1) {
+    bool last = left == 1;
+    if (last && by != kRow) last = atomic_add_dev(&a.multi[mi].w, -1) == 1;
+    for (uint64_t m = __ballot(last); m; m &= m - 1) {
         int4 *q = &a.multi[readlane(mi, __builtin_ctzll(m))];
         const int row = q->x, first = q->y, cnt = q->z;
         Cascade cs;
-        for (int k = lane_id(); k < cnt; k += kWave)
-            cs.add(__hip_atomic_load(&a.partials[first + k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        int k = lane_id();
+        for (; k + (kPartials - 1) * kWave < cnt; k += kPartials * kWave) {
+            float v[kPartials];
+#pragma unroll
+            for (int u = 0; u < kPartials; ++u) v[u] = load_partial(a, first + k + u * kWave);
+#pragma unroll
+            for (int u = 0; u < kPartials; ++u) cs.add(v[u]);
+        }
+        for (; k < cnt; k += kWave) cs.add(load_partial(a, first + k));
         const float s = wave_sum(cs.total());
+        const int counts = row_count(first, cnt);
+        for (int g = lane_id(); cnt > kGroup && g < counts; g += kWave) {
+            const int slot = max(first, (first / kGroup + g) * kGroup);
+            a.groups[group_index(slot, group_of(first, slot))] = group_count(first, cnt, slot);
+        }
         if (lane_id() == 0) {
             a.y[row] = s;
-            q->w = cnt;
+            q->w = counts;
         }
     }
 }
@@ -496,20 +559,28 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(HOT ? 4 :
     const int gw = blockIdx.x * (BLOCK / kWave) + wid;
     const int nw = gridDim.x * (BLOCK / kWave);
     const int lane = lane_id();
-    int t = gw, mi = -1, left = 0;  // lane k: split-row entry of the wave's k-th chunk, the row's count before it was lowered
+    // lane k: split-row entry of the wave's k-th chunk, what counts it, and that count before it was lowered
+    int t = gw, mi = -1, by = kRow, left = 0;
     while (t < chunks) {
-        combine_rows(a, mi, left);  // a wave has more than 64 chunks
+        combine_rows(a, mi, by, left);  // a wave has more than 64 chunks
         mi = -1;
+        by = kRow;
+        int slot = 0;
         for (int k = 0; k < kWave && t < chunks; ++k, t += nw) {
             const int4 d = a.chunks[t];
-            const int row = __builtin_amdgcn_readfirstlane(d.x), from = __builtin_amdgcn_readfirstlane(d.y);
+            const int kind = __builtin_amdgcn_readfirstlane(d.x), from = __builtin_amdgcn_readfirstlane(d.y);
             const int to = __builtin_amdgcn_readfirstlane(d.z), entry = __builtin_amdgcn_readfirstlane(d.w);
             const float s = wave_sum(dot_strided_u<2 * kUnroll>(a, from + lane, kWave, to, s_x.x, nlds));
             if (lane == 0) __hip_atomic_store(&a.partials[t], s, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (lane == k) mi = row < 0 ? -1 : entry;
+            if (lane == k && kind >= 0) {
+                mi = entry;
+                by = kind;
+                slot = t;
+            }
         }
+        int *count = by == kRow ? &a.multi[max(mi, 0)].w : &a.groups[group_index(slot, by - kGroupOf)];
         asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
-        left = mi >= 0 ? atomic_add_dev(&a.multi[mi].w, -1) : 0;
+        left = mi >= 0 ? atomic_add_dev(count, -1) : 0;
     }
     const int bins_end = __builtin_amdgcn_readfirstlane(s_task[kKinds]);
     int kind = 1;
@@ -539,7 +610,7 @@ __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(HOT ? 4 :
             if (r < a.n && end - beg <= a.threshold) a.y[r] = light_row(a, beg, end);
         }
     }
-    combine_rows(a, mi, left);
+    combine_rows(a, mi, by, left);
 }
 
 // ---- small products -----------------------------------------------------------------------------
@@ -836,11 +907,17 @@ wc_status spmv_shape(int num_cus, const wc_csr *g, const float *val, wc_mode mod
     return WC_OK;
 }
 
+// Counts of groups of chunks.
+long long spmv_groups(const SpmvPlan *p)
+{
+    return p->mode == WC_FLAT ? 0 : (p->cap + kGroup - 1) / kGroup * kGroupPad;
+}
+
 // Bytes of workspace the planned product needs (256-byte aligned pieces).
 size_t spmv_workspace_bytes(const SpmvPlan *p)
 {
     return padded(kCols * kPad * 4) + padded(p->rows * 4) + padded(p->basic * 16) + padded(p->cap * 16) + padded(p->cap * 4) +
-           padded(p->mcap * 16);
+           padded(p->mcap * 16) + padded(spmv_groups(p) * 4);
 }
 
 // Lays the workspace out from `base` (256-byte aligned, spmv_workspace_bytes
@@ -860,6 +937,7 @@ char *spmv_carve(SpmvPlan *p, char *base)
     a.chunks = reinterpret_cast<int4 *>(take(p->cap * 16));
     a.partials = reinterpret_cast<float *>(take(p->cap * 4));
     a.multi = reinterpret_cast<int4 *>(take(p->mcap * 16));
+    a.groups = reinterpret_cast<int *>(take(spmv_groups(p) * 4));
     return base + off;
 }
 
