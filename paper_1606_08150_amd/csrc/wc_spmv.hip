@@ -1142,6 +1142,12 @@ extern "C" wc_status wc_pagerank(wc_ctx *ctx, const wc_csr *in_graph, const int3
                              stats, &p);
     if (st != WC_OK) return st;
     if (p.cfg.driver != 0) return fail(WC_EINVAL, "wc_pagerank: only the relaunch driver (driver = 0) applies");
+    // A later sweep of the general path is one launch too (spmv_relaunch), so the
+    // one-launch product, which bins its rows each time, pays in the first sweeps or
+    // where a sweep is all launch.  R-MAT, one-launch / general in us: 2^17 entries, 2
+    // sweeps 28 / 28; 2^16, 3 sweeps 33 / 36, 5 sweeps 53 / 53, 10 sweeps 104 / 97;
+    // 2^15, 10 sweeps 85 / 94; four rows of 30,000 entries, 5 sweeps 130 / 62.
+    p.small = p.small && in_graph->m <= std::max(kSmallNnz / std::max(iterations, 1), 1 << 15);
     PrArgs q;
     q.out_degree = out_degree;
     q.rank = rank;

@@ -1,7 +1,8 @@
 """GPU parity of grid-mode products whose number of rows, not of entries, sets
 their size: both sides of the row limit of the one-launch kernel and of its limit
-for short matrices with many entries (bitwise the general path's sums), and more
-rows than a launch of eight rows to a workgroup could cover."""
+for short matrices with many entries (bitwise the general path's sums), more rows
+than a launch of eight rows to a workgroup could cover, and both sides of the
+limits of PageRank, which depend on the number of sweeps."""
 import numpy as np
 import pytest
 import torch
@@ -51,3 +52,20 @@ def test_more_rows_than_threads_of_a_launch(ctx):
     # all terms are positive: the documented bound of 1e-5 of their sum
     assert ((got - want).abs() <= 1e-5 * want).all()
     assert not y[1:-1].any()
+
+
+@pytest.mark.parametrize("iterations,m", [(1, 1 << 18), (2, 1 << 17), (2, (1 << 17) + 1), (4, 1 << 16),
+                                          (4, (1 << 16) + 1), (9, 1 << 15), (9, (1 << 15) + 1)])
+def test_pagerank_by_sweeps(ctx, iterations, m):
+    n = 3001
+    rng = np.random.default_rng(m)
+    rows = np.where(rng.random(m) < 0.8, rng.integers(0, n, m), 17)
+    ptr = np.concatenate([[0], np.cumsum(np.bincount(rows, minlength=n))]).astype(np.int32)
+    col = rng.integers(0, n - 5, m).astype(np.int32)
+    od = np.bincount(col, minlength=n).astype(np.int32)
+    dg, dod = wc.DeviceCSR.from_host(ptr, col), torch.from_numpy(od).cuda()
+    say(f"pagerank by sweeps: {iterations} m={m}")
+    r = ctx.pagerank(dg, dod, iterations).cpu().numpy()
+    assert oracle.pagerank_check(oracle.pagerank_f64(ptr, col, od, iterations), r)[0] == 0
+    general = ctx.pagerank(dg, dod, iterations, tune=wc.make_tune(**GENERAL)).cpu().numpy()
+    assert np.array_equal(r.view(np.uint32), general.view(np.uint32))
