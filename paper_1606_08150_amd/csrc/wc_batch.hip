@@ -200,6 +200,11 @@ constexpr int kWindowsPerStep = 4;
 // Lanes of a buffered item of up to kShortItem edges, and of a longer one.
 constexpr int kShortItem = 32, kShortLanes = 4, kLongLanes = 16;
 
+// Chunks of a vertex that its own lane writes; more are written by its wave (a
+// vertex of 2^20 edges, 8,192 chunks: 1.88 ms a call by its lane, 0.17 by its wave;
+// the batch of 64 below 1,253 -> 1,112 us).
+constexpr int kOwnChunks = 4;
+
 template <int BLOCK>
 struct BatchLds {
     int list[BLOCK * kWindowsPerStep];
@@ -360,10 +365,23 @@ __global__ __launch_bounds__(BLOCK) void batch_round(BatchArgs a, int r)
             if (tot) {
                 const long long slot = (long long)sb.base + off;
                 if (nch > 0) a.relaxed_at[g] = slot + nch > a.chunk_cap ? t.du : 0u;
-                for (int c = 0; c < nch; ++c) {
+                const int inst = nch > 0 ? find_inst(a, g) : 0;
+                // a few chunks by their own lane, more by the wave
+                const bool many = nch > kOwnChunks && slot + nch <= a.chunk_cap;
+                for (uint64_t m = __ballot(many); m; m &= m - 1) {
+                    const int b = __builtin_ctzll(m);
+                    const int g0 = readlane(g, b), i0 = readlane(inst, b), n0 = readlane(nch, b), k0 = readlane(chunk, b);
+                    const int from = readlane(t.beg, b), to = readlane(t.end, b);
+                    int4 *const out = a.chunks + sb.base + readlane(off, b);
+                    for (int c = lane; c < n0; c += kWave) {
+                        const int cb = from + c * k0;
+                        out[c] = make_int4(g0, cb, min(to, cb + k0), i0);
+                    }
+                }
+                for (int c = 0; c < nch && !many; ++c) {
                     const int cb = t.beg + c * chunk, ce = min(t.end, cb + chunk);
                     if (slot + c < a.chunk_cap) {
-                        a.chunks[slot + c] = make_int4(g, cb, ce, find_inst(a, g));
+                        a.chunks[slot + c] = make_int4(g, cb, ce, inst);
                     } else {
                         a.stats->overflowed = 1;
                         Range part = t;
