@@ -110,6 +110,26 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_wave_barrier();
 }
 
+// ---- one offer a wave and target --------------------------------------------------------------------
+// Where three lanes or more have the target of the first lane that has one (v < 0:
+// none), that lane alone keeps it, with the least of their distances.  All lanes of
+// the wave call.
+__device__ __forceinline__ void one_of_wave(int &v, uint32_t &nd)
+{
+    const uint64_t some = __ballot(v >= 0);
+    if (__builtin_popcountll(some) < 3) return;
+    const int first = __builtin_ctzll(some), target = readlane(v, first);
+    const uint64_t same = __ballot(v == target);
+    if (__builtin_popcountll(same) < 3) return;
+    uint32_t low = v == target ? nd : kInf;
+#pragma unroll
+    for (int d = kWave / 2; d >= 1; d >>= 1) low = min(low, static_cast<uint32_t>(__shfl_xor(static_cast<int>(low), d, kWave)));
+    if (v == target) {
+        v = lane_id() == first ? target : -1;
+        nd = low;
+    }
+}
+
 // ---- wave-aggregated append ---------------------------------------------------------------------
 // Every active lane must call this (it issues a ballot).  Lanes with pred
 // receive distinct consecutive slots starting at the value *tail had; the

@@ -120,25 +120,6 @@ __device__ __forceinline__ void load_quad(const SsspArgs &a, int e, int end, int
     }
 }
 
-// Where three lanes or more have the target of the first lane that has one (v < 0:
-// none), that lane alone keeps it, with the least of their distances.  All lanes of
-// the wave call.
-__device__ __forceinline__ void one_of_wave(int &v, uint32_t &nd)
-{
-    const uint64_t some = __ballot(v >= 0);
-    if (__builtin_popcountll(some) < 3) return;
-    const int first = __builtin_ctzll(some), target = readlane(v, first);
-    const uint64_t same = __ballot(v == target);
-    if (__builtin_popcountll(same) < 3) return;
-    uint32_t low = v == target ? nd : kInf;
-#pragma unroll
-    for (int d = kWave / 2; d >= 1; d >>= 1) low = min(low, static_cast<uint32_t>(__shfl_xor(static_cast<int>(low), d, kWave)));
-    if (v == target) {
-        v = lane_id() == first ? target : -1;
-        nd = low;
-    }
-}
-
 // K loaded edges a lane (v[k] < 0: none), nd[k] the distances they offer.  In grid
 // mode an edge is dropped by the byte that bounds its target's distance, which takes
 // a quarter of the cache and which no atomic touches; the others go to the atomic
