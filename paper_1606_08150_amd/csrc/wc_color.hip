@@ -36,6 +36,7 @@
 #include <algorithm>
 #include <climits>
 #include <cstring>
+#include <type_traits>
 
 #include "wc_block.h"
 #include "wc_device.h"
@@ -336,13 +337,13 @@ enum { kRound = 0, kWide = 1, kDone = 2, kStateInts = 3 };
 // Round r in grid mode: one wave per buffered chunk (a readied vertex's
 // neighbour range, buffered while round r - 1 ran), then one lane per vertex
 // the buffer could not take.  Vertices readied here buffer their ranges for
-// round r + 1.  r < 0: the round that color_narrow found too large for itself,
-// if it did.
-template <int BLOCK>
-__global__ __launch_bounds__(BLOCK) void color_round_grid(ColorArgs a, int r)
+// round r + 1.  Publishes whether it had work.  PHASED (in turn with color_narrow):
+// r < 0 is the round that color_narrow found too large for itself, if it did, and
+// host-ring entry `slot`, unless that is negative, gets the number of chunks.
+template <int BLOCK, bool PHASED>
+__global__ __launch_bounds__(BLOCK) void color_round_grid(ColorArgs a, int r, int slot)
 {
-    const bool narrow = r < 0;
-    if (narrow) {
+    if (PHASED && r < 0) {
         if (!a.state[kWide]) return;
         r = a.state[kRound];
     }
@@ -351,7 +352,8 @@ __global__ __launch_bounds__(BLOCK) void color_round_grid(ColorArgs a, int r)
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         a.chunk_tail[((r + 2) % 3) * kPad] = 0;
         a.qtail[((r + 2) % 3) * kPad] = 0;
-        if (!narrow) publish_host(a.host_ring, r % kHostRing, a.stats, (nchunks != 0 || ndefer != 0) ? 1 : 0);
+        if (!PHASED) publish_host(a.host_ring, r % kHostRing, a.stats, (nchunks != 0 || ndefer != 0) ? 1 : 0);
+        else if (slot >= 0) publish_host(a.host_ring, slot % kHostRing, a.stats, ndefer != 0 ? INT_MAX : nchunks);
     }
     if (nchunks == 0 && ndefer == 0) return;
     const int total = (long long)nchunks < a.chunk_cap ? nchunks : (int)a.chunk_cap;
@@ -390,7 +392,8 @@ __global__ __launch_bounds__(BLOCK) void color_round_grid(ColorArgs a, int r)
 // dozen vertices and release some thousand edges (scale-16 graph, 775 rounds: 50
 // vertices, 4,200 entries in 74 chunks at the median), less than a launch's
 // worth.  The round's chunks are listed in LDS; a wave takes one, two or four of
-// them at a time, and sixteen lanes list the chunks of a vertex readied here.
+// them at a time, and sixteen lanes list the chunks of a vertex readied here (four
+// where there are many).
 // The counts are kept in LDS too, 16 bits each, for the launch.  Bound by the
 // round's two round trips to memory (entries, the readied vertices' ranges) and,
 // beyond some thousand entries, by what one CU's LDS and issue slots take.
@@ -399,23 +402,32 @@ __global__ __launch_bounds__(BLOCK) void color_round_grid(ColorArgs a, int r)
 // 180 and 364 us.  Entries side by side over the threads, each finding its range
 // by a search over prefixes: 5.7 us a round; the counts in memory: 6.9.
 // Rule: graphs of up to kNarrowN vertices, whose counts LDS holds, and rounds of
-// up to kNarrowChunks chunks (at 128, 3,300 instead of 2,450 us on 65,536
-// vertices of 16 edges; at 512 the same).
+// up to kNarrowChunks chunks (at 128, 3,400 instead of 2,420 us on 65,536
+// vertices of 16 edges; at 512 the same), a launch's first of up to kNarrowEnter
+// (128, 160, 192 and 256: 542, 528, 564 and 620 us on 16,384 vertices of 32 random
+// neighbours, 3,605, 3,561, 3,584 and 3,575 on 65,536 of 52) and kNarrowEntries
+// entries.  A launch ends before a round that it finds larger, and after one that
+// readies more vertices than kNarrowChunks.
 // The workgroup starts from, and where a round is larger than it takes leaves,
-// the chunk buffer of the round: color_round_grid does that round
-// (state[kWide]), and the next launch goes on after it.  A launch ends after
-// kNarrowRounds rounds at the latest.  Each launch publishes the number of
-// colored vertices when all is done, -1 when not, and kNarrowBad when a count
-// would go below zero: the graph is not symmetric, packed counts would spill over
-// into their neighbours, and the call is done again without this kernel.
+// the chunk buffer of the round; color_round_grid does that round (state[kWide]),
+// and the next launch goes on after it.  `from` >= 0: the round to start with,
+// where the rounds before were all the grid's.  A launch ends after kNarrowRounds
+// rounds at the latest.  Each launch publishes the number of colored vertices when
+// all is done, kNarrowOn when not, kNarrowIdle - r when it did no round itself but
+// left round r, and kNarrowBad when a count would go below zero: the graph is not
+// symmetric, packed counts would spill over into their neighbours, and the call is
+// done again without this kernel.
 constexpr int kNarrowBlock = 1024;
 constexpr int kNarrowGroup = 16;     // lanes that list one vertex's chunks
+constexpr int kFewLanes = 4;         // ... in a round of more than 64 vertices
 constexpr int kNarrowList = 1024;    // chunks that a list holds
 constexpr int kNarrowChunks = 256;   // chunks of a round that is taken here
+constexpr int kNarrowEnter = 160;    // chunks and
+constexpr int kNarrowEntries = 8192; // entries of a launch's first round
 constexpr int kNarrowChunk = 2 * kWave;  // largest chunk
 constexpr int kNarrowRounds = 4096;
 constexpr int kNarrowN = 65536;
-constexpr int kNarrowBad = -2;
+enum { kNarrowOn = -1, kNarrowBad = -2, kNarrowIdle = -16 };
 // The entries of a round's chunks, U chunks a wave at a time: releases, and the
 // vertices that they ready into s_ready (beyond it: a.queue0).  Each step for all
 // entries before the next: a round trip a step, not one an entry.  True on a
@@ -462,29 +474,52 @@ __device__ __forceinline__ bool narrow_entries(const ColorArgs &a, const int2 *l
     return bad;
 }
 
-__global__ __launch_bounds__(kNarrowBlock) void color_narrow(ColorArgs a, int step)
+// Chunks of the threads' rows side by side at `out`; their number.  The whole
+// workgroup calls.
+__device__ __forceinline__ int list_rows(const ColorArgs &a, int4 *out, int beg, int end, int *s_tmp)
+{
+    const int nch = (end - beg + a.chunk - 1) / a.chunk;
+    int at, unused, tot, unused2;
+    block_scan2<kNarrowBlock>(nch, 0, s_tmp, at, unused, tot, unused2);
+    for (int c = 0; c < nch; ++c) {
+        const int cb = beg + c * a.chunk;
+        out[at + c] = make_int4(0, cb, min(end, cb + a.chunk), 0);
+    }
+    return tot;
+}
+
+__global__ __launch_bounds__(kNarrowBlock) void color_narrow(ColorArgs a, int slot, int from)
 {
     constexpr int NW = kNarrowBlock / kWave;
     __shared__ int2 s_list[2][kNarrowList];
     __shared__ int s_ready[kNarrowBlock];
-    __shared__ int s_next[2], s_found[2];  // chunks of a list, vertices readied
+    __shared__ int s_next[2], s_entries, s_found[2];  // chunks of a list, entries of the first, vertices readied
     __shared__ int s_tmp[2 * NW], s_readied, s_spill, s_listed, s_bad;
     __shared__ unsigned int s_wait[kNarrowN / 2];
     const int tid = threadIdx.x, lane = lane_id();
     const int wid = __builtin_amdgcn_readfirstlane(tid / kWave);
     if (a.state[kDone]) {
-        if (tid == 0) publish_host(a.host_ring, step % kHostRing, a.stats, *a.colored);
+        if (tid == 0) publish_host(a.host_ring, slot % kHostRing, a.stats, *a.colored);
         return;
     }
-    int r = a.state[kRound] + a.state[kWide];  // the wide round, if there was one, is done
+    int r = from >= 0 ? from : a.state[kRound] + a.state[kWide];  // the wide round, if there was one, is done
     const int nchunks = a.chunk_tail[(r % 3) * kPad], ndefer = a.qtail[(r % 3) * kPad];
-    bool fits = ndefer == 0 && nchunks <= kNarrowChunks;
+    bool fits = ndefer == 0 && nchunks <= kNarrowEnter;
     int k = 0;  // rounds done here; the list of the current one is k & 1
     if (tid == 0) {
         s_next[0] = fits ? nchunks : 0;
+        s_entries = 0;
         s_found[0] = s_readied = s_spill = s_bad = 0;
         s_listed = kNarrowList;
     }
+    __syncthreads();
+    if (fits && tid < nchunks) {
+        const int4 d = ((r & 1) ? a.chunks1 : a.chunks)[tid];
+        s_list[0][tid] = make_int2(d.y, d.z);
+        atomicAdd(&s_entries, d.z - d.y);
+    }
+    __syncthreads();
+    fits = fits && s_entries <= kNarrowEntries;
     if (fits && nchunks > 0) {
         bool large = false;
         for (int i = tid; 2 * i < a.n; i += kNarrowBlock) {
@@ -493,14 +528,10 @@ __global__ __launch_bounds__(kNarrowBlock) void color_narrow(ColorArgs a, int st
             large |= (lo | hi) > 0xffffu;
             s_wait[i] = lo | hi << 16;
         }
-        if (tid < nchunks) {
-            const int4 d = ((r & 1) ? a.chunks1 : a.chunks)[tid];
-            s_list[0][tid] = make_int2(d.y, d.z);
-        }
         if (__syncthreads_or(large ? 1 : 0)) fits = false;  // multi-edges: more than 16 bits count
     }
     __syncthreads();
-    int readied = 0;
+    int readied = 0, many = 0;  // many: vertices readied in the last round, where they are not listed
     bool below_zero = false;
     for (; fits && k < kNarrowRounds; ++k, ++r) {
         const int count = s_next[k & 1];
@@ -518,34 +549,42 @@ __global__ __launch_bounds__(kNarrowBlock) void color_narrow(ColorArgs a, int st
         const int found = s_found[k & 1];
         const bool stop = s_bad;  // set before the round's first barrier, read before its second
         if (tid == 0) s_found[(k + 1) & 1] = 0;
+        if (found > kNarrowChunks && !stop) {
+            many = found;
+            ++k, ++r;
+            break;
+        }
         int2 *next = s_list[(k + 1) & 1];
-        const int sub = lane & (kNarrowGroup - 1);
-        for (int i = tid / kNarrowGroup; i < found; i += kNarrowBlock / kNarrowGroup) {
-            const int v = i < kNarrowBlock ? s_ready[i] : a.queue0[min(i - kNarrowBlock, a.n - 1)];
-            const int beg = a.row_ptr[v], end = a.row_ptr[v + 1];
-            const int nch = (end - beg + kNarrowChunk - 1) / kNarrowChunk;
-            int slot = 0;
-            if (sub == 0) {
-                a.color[v] = r + 1;
-                ++readied;
-                slot = atomicAdd(&s_next[(k + 1) & 1], nch);
-            }
-            slot = __shfl(slot, lane & ~(kNarrowGroup - 1), kWave);
-            if (slot + nch <= kNarrowList) {
-                for (int c = sub; c < nch; c += kNarrowGroup) {
-                    const int b = beg + c * kNarrowChunk;
-                    next[slot + c] = make_int2(b, min(end, b + kNarrowChunk));
-                }
-            } else {
-                // more than the list holds (the round is too large anyway): the vertex
-                // to memory; the list ends where the first such vertex would begin
+        auto list_found = [&](auto group) {
+            constexpr int G = decltype(group)::value;  // lanes a vertex
+            const int sub = lane & (G - 1);
+            for (int i = tid / G; i < found; i += kNarrowBlock / G) {
+                const int v = i < kNarrowBlock ? s_ready[i] : a.queue0[min(i - kNarrowBlock, a.n - 1)];
+                const int beg = a.row_ptr[v], end = a.row_ptr[v + 1];
+                const int nch = (end - beg + kNarrowChunk - 1) / kNarrowChunk;
+                int at = 0;
                 if (sub == 0) {
-                    atomicMin(&s_listed, slot);
+                    a.color[v] = r + 1;
+                    ++readied;
+                    at = atomicAdd(&s_next[(k + 1) & 1], nch);
+                }
+                at = __shfl(at, lane & ~(G - 1), kWave);
+                if (at + nch <= kNarrowList) {
+                    for (int c = sub; c < nch; c += G) {
+                        const int b = beg + c * kNarrowChunk;
+                        next[at + c] = make_int2(b, min(end, b + kNarrowChunk));
+                    }
+                } else if (sub == 0) {
+                    // more than the list holds (the round is too large anyway): the vertex
+                    // to memory; the list ends where the first such vertex would begin
+                    atomicMin(&s_listed, at);
                     const int q = atomicAdd(&s_spill, 1);
                     if (q < a.n) a.queue1[q] = v;
                 }
             }
-        }
+        };
+        if (found <= kNarrowBlock / kNarrowGroup) list_found(std::integral_constant<int, kNarrowGroup>{});
+        else list_found(std::integral_constant<int, kFewLanes>{});
         __syncthreads();
         if (stop) {
             below_zero = true;
@@ -554,18 +593,19 @@ __global__ __launch_bounds__(kNarrowBlock) void color_narrow(ColorArgs a, int st
     }
     readied = wave_sum_i(readied);
     if (lane == 0 && readied) atomicAdd(&s_readied, readied);
+    if (tid == 0) atomicAdd(&s_readied, many);
     if (below_zero) {
         // the launches behind this one find nothing to do
         if (tid == 0) {
             *a.colored = kNarrowBad;
             a.state[kWide] = 0;
             a.state[kDone] = 1;
-            publish_host(a.host_ring, step % kHostRing, a.stats, kNarrowBad);
+            publish_host(a.host_ring, slot % kHostRing, a.stats, kNarrowBad);
         }
         return;
     }
     const int count = s_next[k & 1];
-    const bool done = fits && count == 0;
+    const bool done = fits && many == 0 && count == 0;
     int chunks = 0;
     if (k > 0 && !done) {
         for (int i = tid; 2 * i < a.n; i += kNarrowBlock) {
@@ -573,27 +613,35 @@ __global__ __launch_bounds__(kNarrowBlock) void color_narrow(ColorArgs a, int st
             a.wait[2 * i] = (int)(q & 0xffffu);
             if (2 * i + 1 < a.n) a.wait[2 * i + 1] = (int)(q >> 16);
         }
-        // the list becomes the chunk buffer of its round: the chunks of each of its
-        // vertices once, which the buffer holds
         int4 *out = (r & 1) ? a.chunks1 : a.chunks;
-        chunks = min(count, s_listed);
-        if (tid < chunks) out[tid] = make_int4(0, s_list[k & 1][tid].x, s_list[k & 1][tid].y, 0);
-        const int spilled = min(s_spill, a.n);
-        for (int i0 = 0; i0 < spilled; i0 += kNarrowBlock) {
+        if (many == 0) {
+            // the list becomes the chunk buffer of its round: the chunks of each of its
+            // vertices once, which the buffer holds
+            chunks = min(count, s_listed);
+            if (tid < chunks) out[tid] = make_int4(0, s_list[k & 1][tid].x, s_list[k & 1][tid].y, 0);
+            const int spilled = min(s_spill, a.n);
+            for (int i0 = 0; i0 < spilled; i0 += kNarrowBlock) {
+                int beg = 0, end = 0;
+                if (i0 + tid < spilled) {
+                    const int v = a.queue1[i0 + tid];
+                    beg = a.row_ptr[v];
+                    end = a.row_ptr[v + 1];
+                }
+                chunks += list_rows(a, out + chunks, beg, end, s_tmp);
+            }
+        }
+        // more vertices than their round may have chunks: a thread each, and straight
+        // into the round's buffer (16,000 readied by a hub: 250 us by the list)
+        for (int i0 = 0; i0 < many; i0 += kNarrowBlock) {
+            const int i = i0 + tid;
             int beg = 0, end = 0;
-            if (i0 + tid < spilled) {
-                const int v = a.queue1[i0 + tid];
+            if (i < many) {
+                const int v = i < kNarrowBlock ? s_ready[i] : a.queue0[min(i - kNarrowBlock, a.n - 1)];
                 beg = a.row_ptr[v];
                 end = a.row_ptr[v + 1];
+                a.color[v] = r;
             }
-            const int nch = (end - beg + a.chunk - 1) / a.chunk;
-            int at, unused, tot, unused2;
-            block_scan2<kNarrowBlock>(nch, 0, s_tmp, at, unused, tot, unused2);
-            for (int c = 0; c < nch; ++c) {
-                const int cb = beg + c * a.chunk;
-                out[chunks + at + c] = make_int4(0, cb, min(end, cb + a.chunk), 0);
-            }
-            chunks += tot;
+            chunks += list_rows(a, out + chunks, beg, end, s_tmp);
         }
     }
     __syncthreads();
@@ -609,7 +657,7 @@ __global__ __launch_bounds__(kNarrowBlock) void color_narrow(ColorArgs a, int st
     a.state[kRound] = r;
     a.state[kWide] = !done && !(fits && k == kNarrowRounds);
     a.state[kDone] = done;
-    publish_host(a.host_ring, step % kHostRing, a.stats, done ? colored : -1);
+    publish_host(a.host_ring, slot % kHostRing, a.stats, done ? colored : k > 0 ? kNarrowOn : kNarrowIdle - r);
 }
 
 // Clears the rings before the count pass appends to the first queue.
@@ -856,7 +904,7 @@ ColorKernels pick_block(wc_mode mode)
         k.count = reinterpret_cast<const void *>(&color_count<WC_BLOCK, BLOCK>);
         break;
     default:
-        k.round = reinterpret_cast<const void *>(&color_round_grid<BLOCK>);
+        k.round = reinterpret_cast<const void *>(&color_round_grid<BLOCK, false>);
         k.count = reinterpret_cast<const void *>(&color_count<WC_GRID, BLOCK>);
         break;
     }
@@ -968,44 +1016,85 @@ extern "C" wc_status wc_color(wc_ctx *ctx, const wc_csr *g, const uint32_t *prio
     int rounds = 0, launched = 0;
     long long colored = 0;
     // Grid mode, the launch shape, threshold and buffers the library's choice and
-    // nothing counted per round: small rounds by one workgroup, many a launch,
-    // and a grid-wide launch where a round is too large for it.
-    bool narrow = grid_mode && n <= kNarrowN && chunk <= kNarrowChunk && !stats && !cfg.own_shape && !(tune && tune->threshold > 0) &&
-                  cfg.buf_capacity <= 0;
-    while (narrow) {
-        while (launched < rounds + window) {
-            clear_round_slot(ctx, launched);
-            void *nargs[] = {&a, &launched};
-            st = launch(ctx, "color_narrow", reinterpret_cast<const void *>(&color_narrow), dim3(1),
-                        dim3(kNarrowBlock), nargs, stream);
-            int by_state = -1;
-            void *args[] = {&a, &by_state};
-            if (st == WC_OK) st = launch(ctx, names[mode], ks.round, dim3(dgrid), dim3(cfg.block), args, stream);
+    // nothing counted per round: small rounds by one workgroup, many a launch, each
+    // launch with a grid-wide round behind it for the one that is too large.  While
+    // all rounds are too large those launches would be all loss (3 us a round), so
+    // the rounds are the grid's alone, from the start where about n / (mean degree +
+    // 1) vertices have no neighbour above them, and after three idle launches on end,
+    // until one is small enough (16,384 vertices of 32 random neighbours 541 us a call
+    // by the grid alone, 694 by a launch a round, 515 so; 50,000 vertices 787, 1,024
+    // and 786; four hubs joined with 30,000 391, 821 and 391).
+    constexpr int kPhasedBlock = 256;  // the library's choice
+    bool narrow = grid_mode && n <= kNarrowN && chunk <= kNarrowChunk && cfg.block == kPhasedBlock && !stats &&
+                  !cfg.own_shape && !(tune && tune->threshold > 0) && cfg.buf_capacity <= 0;
+    bool done = false;  // with `colored`
+    if (narrow) {
+        bool wide = n * n / (m + n) > kNarrowChunks;
+        int asked = 0, seen = 0;     // results of launches
+        int next = 0, from = 0;      // the grid's next round; the first one of the next small-round launch
+        int idle = 0, c = 0;
+        for (long long steps = 0;; ++steps) {
+            if (steps > 2 * n + 64) return fail(WC_ETIMEOUT, "wc_color: more rounds than vertices");
+            for (; asked < seen + (wide ? window : 2); ++asked) {
+                clear_round_slot(ctx, asked);
+                int r = next, slot = asked;
+                if (wide) {
+                    ++next;
+                } else {
+                    void *nargs[] = {&a, &asked, &from};
+                    st = launch(ctx, "color_narrow", reinterpret_cast<const void *>(&color_narrow), dim3(1),
+                                dim3(kNarrowBlock), nargs, stream);
+                    if (st != WC_OK) return st;
+                    r = slot = from = -1;
+                }
+                void *args[] = {&a, &r, &slot};
+                st = launch(ctx, names[mode], reinterpret_cast<const void *>(&color_round_grid<kPhasedBlock, true>),
+                            dim3(dgrid), dim3(kPhasedBlock), args, stream);
+                if (st != WC_OK) return st;
+            }
+            st = wait_round_count(ctx, seen++, &c);
             if (st != WC_OK) return st;
-            ++launched;
+            if (wide) {
+                if (c == 0) break;
+                if (c <= kNarrowEnter) {
+                    // behind the rounds that are enqueued already
+                    wide = false;
+                    from = next;
+                    seen = asked;
+                    idle = 0;
+                }
+                continue;
+            }
+            idle = c <= kNarrowIdle ? idle + 1 : 0;
+            while (idle >= 3 && c <= kNarrowIdle && seen < asked) {
+                // which round the last of the enqueued launches leaves
+                st = wait_round_count(ctx, seen++, &c);
+                if (st != WC_OK) return st;
+            }
+            if (idle >= 3 && c <= kNarrowIdle) {
+                wide = true;
+                next = kNarrowIdle - c + 1;  // the grid does the one it left
+            }
+            if (c >= 0) {
+                done = true;
+                colored = c;
+                break;
+            }
+            if (c == kNarrowBad) {
+                // what is enqueued behind that launch does nothing
+                st = begin_call(ctx, stream, stats);
+                if (st == WC_OK) st = start();
+                if (st != WC_OK) return st;
+                narrow = false;
+                break;
+            }
         }
-        int c = 0;
-        st = wait_round_count(ctx, rounds, &c);
-        if (st != WC_OK) return st;
-        if (c >= 0) {
-            colored = c;
-            break;
-        }
-        if (c == kNarrowBad) {
-            // what is enqueued behind that launch does nothing
-            st = begin_call(ctx, stream, stats);
-            if (st == WC_OK) st = start();
-            if (st != WC_OK) return st;
-            rounds = launched = 0;
-            narrow = false;
-            break;
-        }
-        if (++rounds > n + 1) return fail(WC_ETIMEOUT, "wc_color: more rounds than vertices");
     }
     while (!narrow) {
         while (launched < rounds + window) {
             clear_round_slot(ctx, launched);
-            void *args[] = {&a, &launched};
+            int no_slot = -1;
+            void *args[] = {&a, &launched, &no_slot};
             st = launch(ctx, names[mode], ks.round, dim3(grid_mode ? dgrid : grid), dim3(cfg.block), args, stream);
             if (st == WC_OK && spills)
                 st = launch(ctx, "color_round_drain", ks.round_drain, dim3(dgrid), dim3(cfg.block), args, stream);
@@ -1021,7 +1110,7 @@ extern "C" wc_status wc_color(wc_ctx *ctx, const wc_csr *g, const uint32_t *prio
         if (!grid_mode && colored > n) return fail(WC_EINVAL, "wc_color: more queued vertices than vertices");
         if (rounds > n + 1) return fail(WC_ETIMEOUT, "wc_color: more rounds than vertices");
     }
-    if (grid_mode && !narrow) {
+    if (grid_mode && !done) {
         // the last round with work colored the vertices of the largest color;
         // a graph without edges has one color and no round with work
         rounds = std::max(rounds, 1);
