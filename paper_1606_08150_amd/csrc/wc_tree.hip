@@ -818,7 +818,7 @@ __device__ __forceinline__ int nodes_before(gptr<const int> child_ptr, int n, lo
 {
     int lo = 0, hi = n;  // the answer lies in [lo, hi]
     while (lo < hi) {
-        const int step = (hi - lo + kWave - 1) / kWave;
+        const int step = (int)(((unsigned int)(hi - lo) + kWave - 1) / kWave);  // hi may be INT_MAX
         const long long q = (long long)lo + (long long)step * lane_id() + step - 1;  // is node q among them?
         const bool in = q < hi && (long long)child_ptr[q + 1] + q + 1 <= d;
         const int c = __builtin_popcountll(__ballot(in));  // monotone: the first c probes hold
@@ -893,8 +893,8 @@ __global__ __launch_bounds__(kTileBlock) void tree_fold_tiles(FoldArgs a)
     int c[E], f[E], own[E];
 #pragma unroll
     for (int k = 0; k < E; ++k) {
-        const int e = e0 + k * kTileBlock + tid;
-        c[k] = e < e1 ? t.child[e] : -1;
+        const unsigned int e = (unsigned int)e0 + k * kTileBlock + tid;  // may pass INT_MAX in the last tiles
+        c[k] = e < (unsigned int)e1 ? t.child[e] : -1;
     }
     const int nn = min(p1, t.n - 1) - p0 + 1;  // nodes p0 .. p1, the last one perhaps only begun here
     for (int i = tid; i <= nn; i += kTileBlock) s_ptr[i] = t.child_ptr[p0 + i];
@@ -907,9 +907,9 @@ __global__ __launch_bounds__(kTileBlock) void tree_fold_tiles(FoldArgs a)
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < E; ++k) {
-        const int e = e0 + k * kTileBlock + tid;
         own[k] = -1;
         if (c[k] >= 0) {
+            const int e = e0 + k * kTileBlock + tid;
             // the node of entry e: the last one whose range begins at or before e
             int lo = 0, hi = nn - 1;
             while (lo < hi) {
