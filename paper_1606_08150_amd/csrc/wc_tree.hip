@@ -778,6 +778,7 @@ struct FoldTree {
     int n;
     int tile0;      // first tile of the tree
     long long base; // first entry of the tree in `word` and `up`
+    long long ready0;  // ... and in `ready`
 };
 
 constexpr int kSole = INT_MIN;
@@ -788,7 +789,7 @@ struct FoldArgs {
     const int *tile_tree;
     unsigned long long *word;  // nodes with children: (children still to come << 32) | fold of the finished ones
     int *up;           // nodes with children: the parent; negative (kSole) where the node is its only inner child
-    int *ready;        // [tiles * kTileReady]: final nodes of each tile
+    int *ready;        // final nodes of each tile: kTileReady entries, a tree's last tile as many as it can use
     int *ready_count;  // [tiles]
     int2 *carry;       // [tiles]: (node whose entries began in an earlier tile or -1, its leaves here)
     unsigned long long *inner;  // a large single tree: bit v set where node v has children; else nullptr
@@ -801,6 +802,7 @@ struct FoldView {
     gptr<int> out;
     gptr<unsigned long long> word;
     gptr<int> up;
+    gptr<int> ready;  // of the tile
     int n, tile0;
 };
 template <bool BATCH>
@@ -808,7 +810,8 @@ __device__ __forceinline__ FoldView fold_view(const FoldArgs &a, int tile)
 {
     const FoldTree &t = BATCH ? a.trees[a.tile_tree[tile]] : a.one;
     return FoldView{global_ptr(t.child_ptr), global_ptr(t.child), global_ptr(t.out),
-                    global_ptr(a.word + t.base), global_ptr(a.up + t.base), t.n, t.tile0};
+                    global_ptr(a.word + t.base), global_ptr(a.up + t.base),
+                    global_ptr(a.ready + t.ready0 + (long long)(tile - t.tile0) * kTileReady), t.n, t.tile0};
 }
 
 // Nodes whose entries (children, then themselves) all lie among the first d
@@ -963,7 +966,7 @@ __global__ __launch_bounds__(kTileBlock) void tree_fold_tiles(FoldArgs a)
             int at = 0;
             if (lane == 0) at = atomicAdd(&s_ready, __builtin_popcountll(m));
             at = readlane(at, 0);
-            if (final_node) a.ready[(long long)tile * kTileReady + at + rank_in(m)] = p;
+            if (final_node) t.ready[at + rank_in(m)] = p;
         }
     }
     __syncthreads();
@@ -977,7 +980,7 @@ __global__ __launch_bounds__(kTileBlock) void tree_fold_climb(FoldArgs a)
     const FoldView t = fold_view<BATCH>(a, tile);
     const int count = a.ready_count[tile];
     for (int j = threadIdx.x; j < count; j += kTileBlock) {
-        const int p = a.ready[(long long)tile * kTileReady + j];
+        const int p = t.ready[j];
         if (p) fold_climb<OP>(t, t.up[p], t.out[p]);
     }
     if (threadIdx.x == kTileBlock - 1) {
@@ -1017,12 +1020,12 @@ TreeKernels<OP, BLOCK> kernels_for(wc_mode mode)
 
 // Fold tiles over one tree or a batch: workspace of the two kernels.
 struct FoldPlan {
-    long long nodes = 0, tiles = 0;
+    long long nodes = 0, tiles = 0, ready = 0;
     long long inner = 0;    // words of the bits of a large single tree
     size_t desc_bytes = 0;  // batch: descriptors and the tree of each tile
     size_t bytes() const
     {
-        return padded(nodes * 8) + padded(nodes * 4) + padded(tiles * kTileReady * 4) + padded(tiles * 4) +
+        return padded(nodes * 8) + padded(nodes * 4) + padded(ready * 4) + padded(tiles * 4) +
                padded(tiles * 8) + padded(inner * 8) + padded(desc_bytes);
     }
 };
@@ -1053,12 +1056,20 @@ __global__ __launch_bounds__(kInnerBlock) void tree_fold_inner(FoldArgs a)
 }
 
 
+// Entries of `ready` of a tree of n nodes.
+long long ready_entries(long long n)
+{
+    const long long entries = 2 * n - 1, full = entries / kTile;
+    return full * kTileReady + (entries % kTile ? entries % kTile / 2 + 1 : 0);
+}
+
 FoldPlan plan_fold(const TreeArgs &a, const std::vector<TreeInst> *batch)
 {
     FoldPlan f;
     auto add = [&](long long n) {
         f.nodes += n;
         f.tiles += (2 * n - 1 + kTile - 1) / kTile;
+        f.ready += ready_entries(n);
     };
     if (!batch) {
         add(a.n);
@@ -1078,12 +1089,12 @@ wc_status run_fold(wc_ctx *ctx, const TreeArgs &t, const FoldPlan &f, const std:
     std::memset(&a, 0, sizeof(a));
     a.word = pool_take<unsigned long long>(ctx, f.nodes);
     a.up = pool_take<int>(ctx, f.nodes);
-    a.ready = pool_take<int>(ctx, f.tiles * kTileReady);
+    a.ready = pool_take<int>(ctx, f.ready);
     a.ready_count = pool_take<int>(ctx, f.tiles);
     a.carry = pool_take<int2>(ctx, f.tiles);
     chain_break(ctx);
     if (!batch) {
-        a.one = FoldTree{t.child_ptr, t.child, t.out, t.n, 0, 0};
+        a.one = FoldTree{t.child_ptr, t.child, t.out, t.n, 0, 0, 0};
         if (f.inner) {
             a.inner = pool_take<unsigned long long>(ctx, f.inner);
             void *iargs[] = {&a};
@@ -1098,15 +1109,16 @@ wc_status run_fold(wc_ctx *ctx, const TreeArgs &t, const FoldPlan &f, const std:
         FoldTree *tr = reinterpret_cast<FoldTree *>(host.data());
         const size_t table = padded(sizeof(FoldTree) * batch->size());
         int *tile_tree = reinterpret_cast<int *>(host.data() + table);
-        long long base = 0;
+        long long base = 0, ready = 0;
         int tile = 0;
         for (size_t i = 0; i < batch->size(); ++i) {
             const TreeInst &b = (*batch)[i];
-            tr[i] = FoldTree{b.child_ptr, b.child, b.out, (int)b.n, tile, base};
+            tr[i] = FoldTree{b.child_ptr, b.child, b.out, (int)b.n, tile, base, ready};
             const int k = (int)((2 * b.n - 1 + kTile - 1) / kTile);
             std::fill(tile_tree + tile, tile_tree + tile + k, (int)i);
             tile += k;
             base += b.n;
+            ready += ready_entries(b.n);
         }
         wc_status st = stage_to_device(ctx, dev, host.data(), f.desc_bytes, stream);
         if (st != WC_OK) return st;
