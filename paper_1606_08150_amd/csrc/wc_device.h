@@ -112,15 +112,15 @@ __device__ __forceinline__ void wave_lds_sync()
 
 // ---- one offer a wave and target --------------------------------------------------------------------
 // Where three lanes or more have the target of the first lane that has one (v < 0:
-// none), that lane alone keeps it, with the least of their distances.  All lanes of
-// the wave call.
-__device__ __forceinline__ void one_of_wave(int &v, uint32_t &nd)
+// none), that lane alone keeps it, with the least of their distances; true then.
+// All lanes of the wave call.
+__device__ __forceinline__ bool one_of_wave(int &v, uint32_t &nd)
 {
     const uint64_t some = __ballot(v >= 0);
-    if (__builtin_popcountll(some) < 3) return;
+    if (__builtin_popcountll(some) < 3) return false;
     const int first = __builtin_ctzll(some), target = readlane(v, first);
     const uint64_t same = __ballot(v == target);
-    if (__builtin_popcountll(same) < 3) return;
+    if (__builtin_popcountll(same) < 3) return false;
     uint32_t low = v == target ? nd : kInf;
 #pragma unroll
     for (int d = kWave / 2; d >= 1; d >>= 1) low = min(low, static_cast<uint32_t>(__shfl_xor(static_cast<int>(low), d, kWave)));
@@ -128,6 +128,7 @@ __device__ __forceinline__ void one_of_wave(int &v, uint32_t &nd)
         v = lane_id() == first ? target : -1;
         nd = low;
     }
+    return true;
 }
 
 // ---- wave-aggregated append ---------------------------------------------------------------------

@@ -133,12 +133,14 @@ __device__ __forceinline__ void load_quad(const SsspArgs &a, int e, int end, int
 // A vertex that very many others point at is offered many distances at once, and
 // its atomics and stores take turns.  With LANES (the parent's light rows: all lanes
 // of the wave are here, with edges of different vertices) the lanes of a wave that
-// share a target make one offer; in the drain, whose lanes have one vertex's edges,
-// the byte is stored only where it falls (in the parent too: 150,001 vertices 1 %
-// slower).  Four vertices joined with all of 30,000: 74 us by reading every
-// distance, 200 by reading none, 76 so; six with all of 2^19: 1.0 to 1.7, 2.5 to 3.5
-// and 0.4 ms; four with 100,000 vertices of 32 edges: 288, 305 and 266 us.  Levels
-// offer the same distance all at once, and there neither gains anything.
+// share a target make one offer, in the second half of the edges only where there
+// were such in the first (all edges every time: 150,001 vertices 2 % slower); in the
+// drain, whose lanes have one vertex's edges, the byte is stored only where it falls
+// (in the parent too: 1 % slower).  Four vertices joined with all of 30,000: 74 us by
+// reading every distance, 200 by reading none, 77 so; six with all of 2^19: 1.0 to
+// 1.7, 2.5 to 3.5 and 0.4 ms; four with 100,000 vertices of 12 edges 225, 267 and
+// 227 us, of 32 288, 305 and 285.  Levels offer the same distance all at once, and
+// there neither gains anything.
 template <bool STAMP, int K, bool LANES = false>
 __device__ __forceinline__ int relax_edges(const SsspArgs &a, int (&v)[K], uint32_t (&nd)[K], int next)
 {
@@ -149,8 +151,13 @@ __device__ __forceinline__ int relax_edges(const SsspArgs &a, int (&v)[K], uint3
 #pragma unroll
         for (int k = 0; k < K; ++k) v[k] = nd[k] < bound_value(code[k]) ? v[k] : -1;
         if (LANES && a.w && !a.want_stats) {  // the counters count every offer
+            bool shared = false;  // among the first half's edges
 #pragma unroll
-            for (int k = 0; k < K; ++k) one_of_wave(v[k], nd[k]);
+            for (int k = 0; k < K / 2; ++k) shared |= one_of_wave(v[k], nd[k]);
+            if (shared) {
+#pragma unroll
+                for (int k = K / 2; k < K; ++k) (void)one_of_wave(v[k], nd[k]);
+            }
         }
     }
 #pragma unroll
