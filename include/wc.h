@@ -25,13 +25,14 @@
  * Conventions shared by every entry point:
  *  - Array arguments are DEVICE pointers owned by the caller; the library never
  *    frees or retains them beyond the call's stream work.
- *  - Work is enqueued on `stream`.  SSSP, BFS, coloring and the trees decide at
- *    run time how many rounds/levels to run: the host waits on device-published
- *    round counts (each tagged with the call's epoch, so a value left by an
- *    earlier call is never taken for this one), and the call returns once the
- *    last round has been enqueued.  The caller synchronizes before reading
- *    outputs, unless `stats` is non-NULL, in which case the call synchronizes
- *    the stream itself to fill it in.
+ *  - Work is enqueued on `stream`.  SSSP, BFS, coloring and the trees level by
+ *    level decide at run time how many rounds/levels to run: the host waits on
+ *    device-published round counts (each tagged with the call's epoch, so a value
+ *    left by an earlier call is never taken for this one), and the call returns
+ *    once the last round has been enqueued.  The products, PageRank, and in grid
+ *    mode the trees and the small graphs of SSSP and BFS as described there, only
+ *    enqueue.  The caller synchronizes before reading outputs, unless `stats` is
+ *    non-NULL, in which case the call synchronizes the stream itself to fill it in.
  *  - Device-side waits (the packet queues of the wave and block modes of the
  *    trees) are bounded in time (2 s by default, wc_ctx_set_wait_limit); a call
  *    containing such waits returns only after its kernels are done and reports
@@ -183,8 +184,9 @@ wc_status wc_ctx_destroy(wc_ctx *ctx);
  * unreachable.  Frontier-driven rounds: every vertex whose distance improved is
  * expanded in the next round; a frontier vertex with more than `threshold`
  * out-edges is consolidated per `mode`, a lighter one relaxes its edges inline.
- * WC_GRID with the library's tune and no stats runs a graph of up to 8,192
- * vertices and 4 to 131,072 edges in one launch (one workgroup, no waiting).
+ * WC_GRID with the library's tune, no stats and no per-kernel timing runs a graph
+ * of up to 8,192 vertices and 4 to 131,072 edges in one launch (one workgroup, no
+ * waiting); with timing on (wc_ctx_set_timing) it runs, and times, the rounds.
  * dist[n] is written entirely.  Distances must stay below UINT32_MAX. */
 wc_status wc_sssp(wc_ctx *ctx, const wc_csr *g, const uint32_t *w, int32_t src, uint32_t *dist, wc_mode mode,
                   const wc_tune *tune, hipStream_t stream, wc_stats *stats);
@@ -206,7 +208,7 @@ wc_status wc_sssp(wc_ctx *ctx, const wc_csr *g, const uint32_t *w, int32_t src, 
  *     (WC_EOVERFLOW instead when tune->allow_fallback < 0).
  *   WC_FLAT, WC_GRID: the calls of one depth (the frontier) are consolidated by
  *     the frontier rounds of wc_sssp with every edge weighing 1, on the same
- *     kernels.
+ *     kernels (small graphs in grid mode in one launch, as there).
  * level[n] is written entirely.  tune->driver must be 0 in wave and block
  * modes, and tune->buffer_alloc 0. */
 wc_status wc_bfs(wc_ctx *ctx, const wc_csr *g, int32_t src, uint32_t *level, wc_mode mode, const wc_tune *tune,

@@ -281,9 +281,10 @@ __device__ __forceinline__ bool relax_buffer(const Range *item, int cap, int ns,
 // Bound by that chain where the frontier is sparse, and by the relaxations' random
 // accesses where it is dense (62M edges relaxed in a batch of 64 power-law graphs of
 // 2^10 to 2^17 vertices, 16 edges each; its random reads run at about 140 G/s).
-// That batch, 16 rounds: block level 1,414 -> 780 us in this kernel and 2.04 ->
-// 1.26 ms a call (thread-strided single edges, a window at a time, generic
-// pointers before), wave level 2.83 -> 1.30 ms, grid level 1.76 -> 1.34 ms.  Lane
+// That batch, 16 rounds: block level 1,414 -> 780 us in this kernel (thread-strided
+// single edges, a window at a time, generic pointers before) and, with the long
+// rows' chunks written by their wave, 1.99 -> 1.08 ms a call, wave level 2.73 ->
+// 1.15 ms, grid level 1.73 -> 1.10 ms.  Lane
 // groups taking adjacent edges instead of quads: 3 % slower in this kernel.  Two
 // or eight windows a step: within 2 % there; 256 graphs 3 % and 1 % slower.
 template <int BLOCK>

@@ -769,7 +769,10 @@ __global__ __launch_bounds__(BLOCK) void sssp_drain(SsspArgs a, int r)
 // 148 -> 29 us, 2,048 168 -> 51, 4,096 175 -> 78, 8,192 192 -> 158; levels 1,024
 // vertices 90 -> 13 us, 4,096 97 -> 34.  One edge a lane and load instead of four
 // consecutive ones: 35, 62, 95 and 217 us.  Half or twice the lanes a vertex: 0 to
-// 10 % slower.
+// 10 % slower.  Other shapes, shortest paths, general path -> this: 8,192 vertices of
+// 4 and of 16 random edges 325 -> 110 and 331 -> 192 us, 1,000 of 64 146 -> 67, 360 of
+// 361 104 -> 67, eight hubs joined with 2,000 87 -> 33, a mesh of 8,000 2,108 -> 549,
+// a star of 8,000 39 -> 38.
 //
 // The limits: LDS ends at 8,192 vertices (16 bytes each), and there a graph of 16
 // edges a vertex (131,072) is still ahead; more edges would pass the general path,
