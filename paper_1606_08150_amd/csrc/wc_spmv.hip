@@ -1148,11 +1148,13 @@ extern "C" wc_status wc_pagerank(wc_ctx *ctx, const wc_csr *in_graph, const int3
     if (st != WC_OK) return st;
     if (p.cfg.driver != 0) return fail(WC_EINVAL, "wc_pagerank: only the relaunch driver (driver = 0) applies");
     // A later sweep of the general path is one launch too (spmv_relaunch), so the
-    // one-launch product, which bins its rows each time, pays in the first sweeps or
-    // where a sweep is all launch.  R-MAT, one-launch / general in us: 2^17 entries, 2
-    // sweeps 28 / 28; 2^16, 3 sweeps 33 / 36, 5 sweeps 53 / 53, 10 sweeps 104 / 97;
-    // 2^15, 10 sweeps 85 / 94; four rows of 30,000 entries, 5 sweeps 130 / 62.
-    p.small = p.small && in_graph->m <= std::max(kSmallNnz / std::max(iterations, 1), 1 << 15);
+    // one-launch product, which bins its rows every time, pays in the first sweeps, the
+    // more of them the fewer its workgroups.  R-MAT, one-launch / general in us: 16,384
+    // vertices of 12 edges 2 sweeps 28.9 / 28.2, 3 sweeps 42 / 37; 10,547 of 9, 4 sweeps
+    // 44 / 44, 5 sweeps 54 / 53; 4,096 of 16, 3 sweeps 34 / 35, 10 sweeps 104 / 92 (of 8
+    // edges 85 / 94); uniform, 16,384 of 4, 2 sweeps 23 / 28, 5 sweeps 51 / 49; four
+    // rows of 30,000 entries, 5 sweeps 130 / 62.
+    p.small = p.small && n * iterations <= 3 << 14;
     PrArgs q;
     q.out_degree = out_degree;
     q.rank = rank;
